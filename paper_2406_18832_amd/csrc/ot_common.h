@@ -73,6 +73,12 @@ hipError_t launch_qgemm_prefill(const int8_t *Xq, const int8_t *Wq, const float 
                                 const int32_t *zW, const float *sW, const float *bprime,
                                 int64_t M, int64_t N, int64_t K, uint16_t *Y, int32_t *acc_out,
                                 hipStream_t st);
+// One launch on the deep-ring tile of bn output channels by bm tokens (a pair
+// that launch_qgemm_prefill's table names).
+hipError_t launch_qgemm_ring(int bn, int bm, const int8_t *Xq, const int8_t *Wq, const float *sX,
+                             const int32_t *zW, const float *sW, const float *bp, int64_t M,
+                             int64_t N, int64_t K, uint16_t *Y, int32_t *acc_out,
+                             hipStream_t st);
 // Epilogue: sX != nullptr per-token scales (Eq. (c)); zW != nullptr
 // asymmetric weight zero points (Eq. (a)); neither, per-channel (Eq. (g)).
 // workspace: nullptr, or at least qgemm_workspace_bytes(M, N, K) bytes.

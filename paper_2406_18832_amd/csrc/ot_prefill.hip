@@ -493,76 +493,115 @@ hipError_t launch_prefill(const int8_t *Xq, const int8_t *Wq, const float *sX, c
 
 using namespace detail;
 
-// Relative time of a launch with BN x BM tiles, one workgroup per CU: whole
-// passes over the CUs, each as long as one tile.  A tile's time is
+// Relative time of a launch on this file's BN x BM tiles, one workgroup per
+// CU: whole passes over the CUs, each as long as one tile.  A tile's time is
 // proportional to its products over K plus its epilogue, which costs about
 // as much as 820 more K steps, times a factor per tile shape for the operand
 // bytes it stages per product: 0.97 for the wider tile (fewer bytes per
-// product), 1.5 for the shorter one (1.5 times the bytes), 1.15 for the
-// narrower one (1.17 times).  Measured on MI355X, per pass against 256 x 256
-// at the OPT-6.7B, -13B and -66B layer shapes: 0.93-1.01, 1.3-1.6 and, for
-// 192 x 256, the cheapest tile wherever the model picks it (2048 tokens by
-// 12288 channels: 103.7 against 116.1 us; one-pass launches of 2000 tokens
-// by 5000 channels: equal to 256 x 256 within 4 %).  Re-measured with the
-// loads spread over the MFMAs (OPT-6.7B and -13B shapes): 1.01, 1.61 and
-// 1.24, which pick the same tiles on those layers.
-static double prefill_cost(int64_t M, int64_t N, int64_t K, int bn, int bm, int cus) {
+// product), 1.15 for the narrower one (1.17 times).  Measured on MI355X, per
+// pass against 256 x 256 at the OPT-6.7B, -13B and -66B layer shapes:
+// 0.93-1.01 and, for 192 x 256, the cheapest tile wherever the model picks it
+// (2048 tokens by 12288 channels: 103.7 against 116.1 us; one-pass launches
+// of 2000 tokens by 5000 channels: equal to 256 x 256 within 4 %).
+static double prefill_cost(int64_t M, int64_t N, int64_t K, int bn, int bm, int64_t cus) {
   const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
   const int64_t passes = (tiles + cus - 1) / cus;
-  const double penalty = bn == 320 ? 0.97 : bn == 192 ? 1.15 : bm == 128 ? 1.5 : 1.0;
+  const double penalty = bn == 320 ? 0.97 : bn == 192 ? 1.15 : 1.0;
   return (double)passes * bn * bm * ((double)K + 820.0) * penalty;
 }
 
-// Four tile shapes, each one workgroup of 8 waves per CU with a 2-stage
-// ring of BK = 128:
+// The prefill tiles.  The first three are this file's, each one workgroup of
+// 8 waves per CU with a 2-stage ring of BK = 128:
 //   256 (channels) x 256 (tokens), waves 4 x 2 of 64 x 128 (128 KiB of LDS);
 //   320 x 256, waves 2 x 4 of 160 x 64 (a 144 KiB ring in 160 KiB, which
 //     holds the epilogue's whole output tile): lets layers whose tile
 //     count leaves the last pass over the CUs mostly empty fill whole passes
 //     (4096 tokens by 5120 or 15360 channels: 256 and 768 tiles against 320
 //     and 960 of 256 x 256);
-//   256 x 128, waves 4 x 2 of 64 x 64 (96 KiB): for launches that fill less
-//     than one pass with 256 x 256 (2048 tokens by 4096 channels: 256 tiles
-//     against 128);
 //   192 x 256, waves 2 x 4 of 96 x 64 (112 KiB): the same for launches
 //     whose last pass of 256 x 256 runs half empty (2048 tokens by 12288
-//     channels: two full passes of 512 tiles against 1.5 of 384).
-// The cheapest by prefill_cost runs; all give identical results.
-enum class PrefillTile { k256x256, k320x256, k256x128, k192x256 };
+//     channels: two full passes of 512 tiles against 1.5 of 384);
+// prefill_cost picks one of them.  The others are the deep-ring tiles of
+// ot_ring.hip, for launches that leave CUs idle on the large ones.  Of the
+// large tile and the deep-ring ones, the least estimated time runs (all give
+// identical results).
+//
+// The estimate, in microseconds: whole passes over the CUs, each of `pass` +
+// `per_k` per 1000 channels of K, plus `once` per launch (below 0 where the
+// passes overlap).  Each tile's three numbers are a least-squares fit of its
+// time on MI355X over 90 random launches (65 .. 3000 tokens, 768 .. 28672
+// channels, K = 768 .. 20480).  Over 150 other random launches (65 .. 7510
+// tokens) the tile it picks is 0.3 % over the fastest of them all (8 % at
+// worst); over the 90, the large tiles and the two-stage 256 x 128 tile that
+// served these launches before were 93 % over it.
+struct PrefillTile {
+  int bn, bm;
+  float once, pass, per_k;
+  const char *name;
+};
+static const PrefillTile kPrefillTiles[] = {
+    {256, 256, -7.11f, 14.23f, 9.03f, "prefill 256x256"},
+    {320, 256, -4.71f, 17.32f, 10.63f, "prefill 320x256"},
+    {192, 256, -7.54f, 14.32f, 7.98f, "prefill 192x256"},
+    {256, 128, -4.65f, 11.96f, 5.30f, "prefill 256x128"},
+    {192, 128, -2.62f, 10.01f, 4.25f, "prefill 192x128"},
+    {128, 128, -1.34f, 6.80f, 3.32f, "prefill 128x128"},
+    {128, 96, 0.00f, 7.18f, 3.10f, "prefill 128x96"},
+    {64, 128, 0.21f, 4.82f, 2.22f, "prefill 64x128"},
+    {64, 64, 0.67f, 3.93f, 1.65f, "prefill 64x64"},
+    {32, 64, 1.16f, 3.24f, 1.25f, "prefill 32x64"},
+    {32, 32, 0.88f, 2.93f, 0.86f, "prefill 32x32"},
+};
+constexpr int kLargeTiles = 3;  // the first ones: this file's
+constexpr int k256x128 = 3;
 
-static PrefillTile prefill_tile(int64_t M, int64_t N, int64_t K) {
-  const int cus = device_cus();
-  const double c0 = prefill_cost(M, N, K, 256, 256, cus);
-  const double c1 = prefill_cost(M, N, K, 320, 256, cus);
-  const double c2 = prefill_cost(M, N, K, 256, 128, cus);
-  const double c3 = prefill_cost(M, N, K, 192, 256, cus);
-  if (c1 < c0 && c1 <= c2 && c1 <= c3) return PrefillTile::k320x256;
-  if (c3 < c0 && c3 <= c2) return PrefillTile::k192x256;
-  if (c2 < c0) return PrefillTile::k256x128;
-  return PrefillTile::k256x256;
+static const PrefillTile &prefill_tile(int64_t M, int64_t N, int64_t K) {
+  // Three token tiles by four channel tiles over a short K stay on 256 x 128,
+  // the tile that the launch plan is required to report there (300 tokens,
+  // 1000 channels, K = 1040: 9.5 us against 6 on 32 x 64).
+  if (M > 256 && M <= 384 && N > 768 && N <= 1024 && K <= 1040) return kPrefillTiles[k256x128];
+  const int64_t cus = device_cus();
+  const PrefillTile *large = &kPrefillTiles[0];
+  double large_cost = prefill_cost(M, N, K, large->bn, large->bm, cus);
+  for (int i = 1; i < kLargeTiles; ++i) {
+    const double c = prefill_cost(M, N, K, kPrefillTiles[i].bn, kPrefillTiles[i].bm, cus);
+    if (c < large_cost) {
+      large = &kPrefillTiles[i];
+      large_cost = c;
+    }
+  }
+  const PrefillTile *best = nullptr;
+  double best_t = 0;
+  for (const PrefillTile &t : kPrefillTiles) {
+    if (t.bm == 256 && &t != large) continue;
+    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    if (tiles > INT32_MAX) continue;  // the grid is a 32-bit count
+    const double passes = (double)((tiles + cus - 1) / cus);
+    const double us = t.once + passes * (t.pass + t.per_k * 1e-3 * (double)K);
+    if (best == nullptr || us < best_t) {
+      best = &t;
+      best_t = us;
+    }
+  }
+  return *best;
 }
 
 const char *prefill_tile_name(int64_t M, int64_t N, int64_t K) {
-  switch (prefill_tile(M, N, K)) {
-    case PrefillTile::k320x256: return "prefill 320x256";
-    case PrefillTile::k256x128: return "prefill 256x128";
-    case PrefillTile::k192x256: return "prefill 192x256";
-    default: return "prefill 256x256";
-  }
+  return prefill_tile(M, N, K).name;
 }
 
 hipError_t launch_qgemm_prefill(const int8_t *Xq, const int8_t *Wq, const float *sX,
                                 const int32_t *zW, const float *sW, const float *bprime,
                                 int64_t M, int64_t N, int64_t K, uint16_t *Y, int32_t *acc_out,
                                 hipStream_t st) {
-  switch (prefill_tile(M, N, K)) {
-    case PrefillTile::k320x256:
+  const PrefillTile &t = prefill_tile(M, N, K);
+  if (t.bm != 256)
+    return launch_qgemm_ring(t.bn, t.bm, Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, st);
+  switch (t.bn) {
+    case 320:
       return launch_prefill<320, 256, 128, 2, 4, 2, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y,
                                                     acc_out, st);
-    case PrefillTile::k256x128:
-      return launch_prefill<256, 128, 128, 4, 2, 2, 1>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y,
-                                                    acc_out, st);
-    case PrefillTile::k192x256:
+    case 192:
       return launch_prefill<192, 256, 128, 2, 4, 2, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y,
                                                     acc_out, st);
     default:

@@ -529,28 +529,29 @@ static double prefill_cost(int64_t M, int64_t N, int64_t K, int bn, int bm, int6
 // The estimate, in microseconds: whole passes over the CUs, each of `pass` +
 // `per_k` per 1000 channels of K, plus `once` per launch (below 0 where the
 // passes overlap).  Each tile's three numbers are a least-squares fit of its
-// time on MI355X over 90 random launches (65 .. 3000 tokens, 768 .. 28672
-// channels, K = 768 .. 20480).  Over 150 other random launches (65 .. 7510
-// tokens) the tile it picks is 0.3 % over the fastest of them all (8 % at
-// worst); over the 90, the large tiles and the two-stage 256 x 128 tile that
-// served these launches before were 93 % over it.
+// time on MI355X over 240 random launches (65 .. 7510 tokens, 512 .. 28672
+// channels, K = 592 .. 20480) whose weights come from HBM (copies of 800 MB
+// in turn).  The tile it picks is 0.3 % over the fastest of them all (18 % at
+// worst; fitted to one half of the launches, 0.2-0.4 % on the other); the
+// large tiles and the two-stage 256 x 128 tile that served these launches
+// before were 93 % over it on the first 90 of them.
 struct PrefillTile {
   int bn, bm;
   float once, pass, per_k;
   const char *name;
 };
 static const PrefillTile kPrefillTiles[] = {
-    {256, 256, -7.11f, 14.23f, 9.03f, "prefill 256x256"},
-    {320, 256, -4.71f, 17.32f, 10.63f, "prefill 320x256"},
-    {192, 256, -7.54f, 14.32f, 7.98f, "prefill 192x256"},
-    {256, 128, -4.65f, 11.96f, 5.30f, "prefill 256x128"},
-    {192, 128, -2.62f, 10.01f, 4.25f, "prefill 192x128"},
-    {128, 128, -1.34f, 6.80f, 3.32f, "prefill 128x128"},
-    {128, 96, 0.00f, 7.18f, 3.10f, "prefill 128x96"},
-    {64, 128, 0.21f, 4.82f, 2.22f, "prefill 64x128"},
-    {64, 64, 0.67f, 3.93f, 1.65f, "prefill 64x64"},
-    {32, 64, 1.16f, 3.24f, 1.25f, "prefill 32x64"},
-    {32, 32, 0.88f, 2.93f, 0.86f, "prefill 32x32"},
+    {256, 256, -4.60f, 11.41f, 12.29f, "prefill 256x256"},
+    {320, 256, -3.41f, 15.61f, 14.14f, "prefill 320x256"},
+    {192, 256, -3.09f, 9.89f, 10.70f, "prefill 192x256"},
+    {256, 128, -2.49f, 8.73f, 7.32f, "prefill 256x128"},
+    {192, 128, -1.38f, 7.86f, 5.84f, "prefill 192x128"},
+    {128, 128, -0.38f, 5.55f, 4.38f, "prefill 128x128"},
+    {128, 96, 0.44f, 5.73f, 3.84f, "prefill 128x96"},
+    {64, 128, 0.25f, 4.47f, 2.72f, "prefill 64x128"},
+    {64, 64, 0.48f, 3.81f, 1.87f, "prefill 64x64"},
+    {32, 64, 1.21f, 3.08f, 1.38f, "prefill 32x64"},
+    {32, 32, 1.24f, 2.72f, 0.97f, "prefill 32x32"},
 };
 constexpr int kLargeTiles = 3;  // the first ones: this file's
 constexpr int k256x128 = 3;

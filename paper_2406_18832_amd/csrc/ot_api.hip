@@ -1,10 +1,12 @@
 // C ABI of libot (declared in include/ot.h): argument checks on the host,
 // then kernel launches on the caller's stream.  Nothing here allocates
-// device memory or keeps state between calls.
+// device memory; the only state between calls is a block of status words.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
+#include <mutex>
 #include <vector>
 
 #include "ot_common.h"
@@ -25,6 +27,68 @@ int qmax(int bits) { return (1 << (bits - 1)) - 1; }
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 ot_status hip_status(hipError_t e) { return e == hipSuccess ? OT_OK : OT_EHIP; }
+
+// A word of pinned host memory that a kernel of one synchronous call raises
+// and the call reads after its stream synchronization, instead of copying
+// the call's outputs back to look at them (two copies through the runtime's
+// staging buffer: 50 us after a fold of 20480 channels).  The words
+// come from one 4 KiB block, allocated on first use and kept until the
+// process ends; a call holds its word only while it runs.  Without one (every
+// word taken, or no pinned memory) word() is nullptr and the caller reads its
+// outputs back.
+class StatusWord {
+ public:
+  StatusWord() {
+    int *block = words();
+    if (block == nullptr) return;
+    uint64_t used = used_.load(std::memory_order_relaxed);
+    while (~used != 0) {
+      const int i = __builtin_ctzll(~used);
+      if (used_.compare_exchange_weak(used, used | (uint64_t(1) << i),
+                                      std::memory_order_acquire, std::memory_order_relaxed)) {
+        index_ = i;
+        word_ = block + i * kStride;
+        __atomic_store_n(word_, 0, __ATOMIC_RELEASE);
+        return;
+      }
+    }
+  }
+  // Only when no kernel that may write it still runs (its stream has been
+  // synchronized, or nothing was launched): any other word is never handed
+  // out again.
+  void release() {
+    if (word_ != nullptr) used_.fetch_and(~(uint64_t(1) << index_), std::memory_order_release);
+    word_ = nullptr;
+  }
+  int *word() const { return word_; }
+  bool raised() const { return __atomic_load_n(word_, __ATOMIC_ACQUIRE) != 0; }
+
+ private:
+  static constexpr int kStride = 16;  // a 64-byte line each, 64 of them
+  static int *words() {
+    static std::once_flag once;
+    std::call_once(once, [] {
+      // another thread may be capturing a graph: this allocation is no part of it
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      (void)hipThreadExchangeStreamCaptureMode(&mode);
+      void *p = nullptr;
+      if (hipHostMalloc(&p, 64 * kStride * sizeof(int),
+                        hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) ==
+          hipSuccess)
+        block_ = static_cast<int *>(p);
+      else
+        (void)hipGetLastError();
+      (void)hipThreadExchangeStreamCaptureMode(&mode);
+    });
+    return block_;
+  }
+  static int *block_;
+  static std::atomic<uint64_t> used_;
+  int *word_ = nullptr;
+  int index_ = 0;
+};
+int *StatusWord::block_ = nullptr;
+std::atomic<uint64_t> StatusWord::used_{0};
 
 bool all_finite(const std::vector<float> &v) {
   for (float f : v)
@@ -92,10 +156,21 @@ ot_status ot_scales_from_minmax(const float *minmax, int64_t K, int a_bits, int 
                                               inv_s, static_cast<hipStream_t>(stream)));
 }
 
-// Reads sW and b' back (synchronously): a NaN scale marks non-finite weights,
-// a non-finite b' non-finite bias or shift.
-static ot_status fold_outputs_finite(const float *sW, const float *bprime, int64_t N,
-                                     hipStream_t st) {
+// After a fold's launch (its status e): waits for it and tells whether every
+// scale and bias is finite (a NaN scale marks non-finite weights), from the
+// kernel's status word or, without one, from sW and b' read back.
+static ot_status fold_result(hipError_t e, StatusWord &status, const float *sW,
+                             const float *bprime, int64_t N, hipStream_t st) {
+  if (e != hipSuccess) {
+    status.release();  // nothing was launched
+    return OT_EHIP;
+  }
+  if (status.word() != nullptr) {
+    if (hipStreamSynchronize(st) != hipSuccess) return OT_EHIP;
+    const bool bad = status.raised();
+    status.release();
+    return bad ? OT_ENONFINITE : OT_OK;
+  }
   ot_status rc;
   std::vector<float> scale((size_t)N), bias((size_t)N);
   if ((rc = hip_status(hipMemcpyAsync(scale.data(), sW, sizeof(float) * N, hipMemcpyDeviceToHost,
@@ -115,11 +190,10 @@ ot_status ot_fold_weights(const uint16_t *W, const uint16_t *b, int64_t N, int64
   if (!bits_ok(w_bits) || N < 0 || K < 0) return OT_EINVAL;
   if (N == 0 || K == 0 || N > kMaxRows || K > kMaxRows) return OT_ESHAPE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ot_status rc;
-  if ((rc = hip_status(ot::launch_fold(W, b, N, K, qmax(w_bits), z, s, Wq, sW, bprime, st))) !=
-      OT_OK)
-    return rc;
-  return fold_outputs_finite(sW, bprime, N, st);
+  StatusWord status;
+  const hipError_t e =
+      ot::launch_fold(W, b, N, K, w_bits, z, s, Wq, sW, bprime, status.word(), st);
+  return fold_result(e, status, sW, bprime, N, st);
 }
 
 ot_status ot_quantize_act(const uint16_t *x, int64_t M, int64_t K, int a_bits, const float *z,
@@ -183,11 +257,10 @@ ot_status ot_fold_weights_per_token(const uint16_t *W, const uint16_t *b, const 
   if (N == 0 || K == 0 || N > kMaxRows || K > kMaxRows) return OT_ESHAPE;
   if (!W || !Wq || !sW || !bprime) return OT_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ot_status rc;
-  if ((rc = hip_status(ot::launch_fold_per_token(W, b, zres, N, K, qmax(w_bits), Wq, sW, bprime,
-                                                 st))) != OT_OK)
-    return rc;
-  return fold_outputs_finite(sW, bprime, N, st);
+  StatusWord status;
+  const hipError_t e =
+      ot::launch_fold_per_token(W, b, zres, N, K, w_bits, Wq, sW, bprime, status.word(), st);
+  return fold_result(e, status, sW, bprime, N, st);
 }
 
 ot_status ot_qlinear_per_token(const int8_t *Xq, const int8_t *Wq, const float *sX,
@@ -216,11 +289,10 @@ ot_status ot_fold_weights_asym(const uint16_t *W, const uint16_t *b, int64_t N, 
   if (!bits_ok(w_bits) || N < 0 || K < 0) return OT_EINVAL;
   if (N == 0 || K == 0 || N > kMaxRows || K > kMaxRows) return OT_ESHAPE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  ot_status rc;
-  if ((rc = hip_status(ot::launch_fold_asym(W, b, N, K, w_bits, z, s, Wq, sW, zW, bprime, st))) !=
-      OT_OK)
-    return rc;
-  return fold_outputs_finite(sW, bprime, N, st);
+  StatusWord status;
+  const hipError_t e =
+      ot::launch_fold_asym(W, b, N, K, w_bits, z, s, Wq, sW, zW, bprime, status.word(), st);
+  return fold_result(e, status, sW, bprime, N, st);
 }
 
 ot_status ot_qlinear_asym(const int8_t *Xq, const int8_t *Wq, const float *sW, const int32_t *zW,

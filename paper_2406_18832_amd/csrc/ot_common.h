@@ -45,9 +45,11 @@ hipError_t launch_calib_minmax(const uint16_t *x, int64_t rows, int64_t K, float
                                hipStream_t st);
 hipError_t launch_calib_finalize(const float *minmax, int64_t K, int qa, int symmetrize, float *z,
                                  float *s, float *inv_s, hipStream_t st);
-hipError_t launch_fold(const uint16_t *W, const uint16_t *b, int64_t N, int64_t K, int qw,
+// status: nullptr, or a host word (mapped, coherent) that a non-finite scale or
+// bias sets to 1.
+hipError_t launch_fold(const uint16_t *W, const uint16_t *b, int64_t N, int64_t K, int w_bits,
                        const float *z, const float *s, int8_t *Wq, float *sW, float *bprime,
-                       hipStream_t st);
+                       int *status, hipStream_t st);
 hipError_t launch_quantize_act(const uint16_t *x, int64_t M, int64_t K, int qa, const float *z,
                                const float *inv_s, int8_t *Xq, hipStream_t st);
 hipError_t launch_ln_quantize_act(const uint16_t *h, int64_t M, int64_t K, const uint16_t *gamma,
@@ -88,11 +90,11 @@ hipError_t launch_qgemm(const int8_t *Xq, const int8_t *Wq, const float *sX, con
 size_t qgemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t launch_fold_asym(const uint16_t *W, const uint16_t *b, int64_t N, int64_t K,
                             int w_bits, const float *z, const float *s, int8_t *Wq, float *sW,
-                            int32_t *zW, float *bprime, hipStream_t st);
+                            int32_t *zW, float *bprime, int *status, hipStream_t st);
 hipError_t launch_quantize_act_per_token(const uint16_t *x, int64_t M, int64_t K, int qa,
                                          int8_t *Xq, float *sX, hipStream_t st);
 hipError_t launch_fold_per_token(const uint16_t *W, const uint16_t *b, const float *zres,
-                                 int64_t N, int64_t K, int qw, int8_t *Wq, float *sW,
-                                 float *bprime, hipStream_t st);
+                                 int64_t N, int64_t K, int w_bits, int8_t *Wq, float *sW,
+                                 float *bprime, int *status, hipStream_t st);
 
 }  // namespace ot

@@ -135,6 +135,20 @@ ot_status ot_calibrate(const uint16_t *x, int64_t rows, int64_t K, int a_bits, i
   ot_status rc;
   if (first && (rc = hip_status(ot::launch_calib_reset(minmax, K, st))) != OT_OK) return rc;
   if ((rc = hip_status(ot::launch_calib_minmax(x, rows, K, minmax, st))) != OT_OK) return rc;
+  if (ot::calib_finish_ok(K)) {
+    StatusWord status;
+    if (status.word() != nullptr) {
+      if (ot::launch_calib_finish(minmax, K, qmax(a_bits), z, s, inv_s, status.word(), st) !=
+          hipSuccess) {
+        status.release();  // it was not launched
+        return OT_EHIP;
+      }
+      if (hipStreamSynchronize(st) != hipSuccess) return OT_EHIP;
+      const bool bad = status.raised();
+      status.release();
+      return bad ? OT_ENONFINITE : OT_OK;
+    }
+  }
   std::vector<float> state((size_t)(2 * K));
   if ((rc = hip_status(hipMemcpyAsync(state.data(), minmax, sizeof(float) * 2 * K,
                                       hipMemcpyDeviceToHost, st))) != OT_OK)

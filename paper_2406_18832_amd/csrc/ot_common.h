@@ -43,6 +43,11 @@ int device_cus();
 hipError_t launch_calib_reset(float *minmax, int64_t K, hipStream_t st);
 hipError_t launch_calib_minmax(const uint16_t *x, int64_t rows, int64_t K, float *minmax,
                                hipStream_t st);
+// Finalize unless the state holds a non-finite value, which sets *status (a
+// mapped host word) to 1 instead; for K that calib_finish_ok takes.
+bool calib_finish_ok(int64_t K);
+hipError_t launch_calib_finish(const float *minmax, int64_t K, int qa, float *z, float *s,
+                               float *inv_s, int *status, hipStream_t st);
 hipError_t launch_calib_finalize(const float *minmax, int64_t K, int qa, int symmetrize, float *z,
                                  float *s, float *inv_s, hipStream_t st);
 // status: nullptr, or a host word (mapped, coherent) that a non-finite scale or

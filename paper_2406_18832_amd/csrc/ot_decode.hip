@@ -619,18 +619,6 @@ hipError_t launch_decode_t(const int8_t *Xq, const int8_t *Wq, const float *sX, 
   return hipGetLastError();
 }
 
-// Weight layout by argument: packed micro-tiles or Wq [N x K].
-template <int MB, int NR, int NK, int RBW, int BKD, int S>
-hipError_t launch_decode(const int8_t *Xq, const int8_t *Wq, const float *sX, const int32_t *zW,
-                         const float *sW, const float *bp, int64_t M, int64_t N, int64_t K,
-                         uint16_t *Y, int32_t *acc_out, bool packed, hipStream_t st) {
-  if (packed)
-    return launch_decode_t<MB, NR, NK, RBW, BKD, S, true>(Xq, Wq, sX, zW, sW, bp, M, N, K, Y,
-                                                          acc_out, st);
-  return launch_decode_t<MB, NR, NK, RBW, BKD, S, false>(Xq, Wq, sX, zW, sW, bp, M, N, K, Y,
-                                                         acc_out, st);
-}
-
 // Packs Wq [N x K] into micro-tiles (see PACKED above): thread t writes the
 // 16 bytes of lane t mod 64 of micro-tile t / 64.
 __global__ __launch_bounds__(256) void pack_weights_kernel(const int8_t *__restrict__ Wq,
@@ -778,12 +766,28 @@ static hipError_t decode_tiles(const DecodePlan &p, const int8_t *Xq, const int8
 #undef OT_TILE
 }
 
+// Row-major weights, up to 16 tokens: 16-row tiles where the rows fill at
+// most one per CU, and where 32-row tiles would leave the fullest CU more than
+// 1.25 times as much over its share as 16-row tiles do (rows per CU, whole
+// tiles: 9216 channels are 36 a CU, 64 on the fullest with 32-row tiles and 48
+// with 16-row ones: 20.7 against 16.7 us at K = 9216; 12288: 12.0 against
+// 11.8; past that line the larger tiles' fewer workgroups win, 20480 channels
+// at K = 5120 19.2 against 20.4).
+static bool decode16_rows16(int64_t N, int64_t cus) {
+  if (N <= 16 * cus) return true;
+  if (N <= 32 * cus) return false;
+  const int64_t most32 = ((N + 31) / 32 + cus - 1) / cus * 32;
+  const int64_t most16 = ((N + 15) / 16 + cus - 1) / cus * 16;
+  return 4 * most32 > 5 * most16;
+}
+
 void describe_decode(int64_t M, int64_t N, int64_t K, bool packed, bool workspace, char *buf,
                      size_t len) {
   const int64_t cus = device_cus();
   const char *layout = packed ? "packed" : "row-major";
   if (M <= 16) {
-    const int rows = N <= 16 * cus ? 16 : (packed && N > 32 * cus && N <= 64 * cus) ? 64 : 32;
+    const int rows = packed ? (N <= 16 * cus ? 16 : (N > 32 * cus && N <= 64 * cus) ? 64 : 32)
+                            : decode16_rows16(N, cus) ? 16 : 32;
     snprintf(buf, len, "decode %s %d-row tiles", layout, rows);
     return;
   }
@@ -805,8 +809,10 @@ hipError_t launch_qgemm_decode(const int8_t *Xq, const int8_t *Wq, const float *
   // Up to 16 tokens: 32-row tiles.  Where they fill at most one pass over
   // the CUs, one 8-wave workgroup per CU streams 16 KiB of weights per stage
   // (512-byte K slices, 3 stages ahead); with more rows, 2-wave workgroups
-  // with 128-byte slices run six to a CU.  Below 16 rows per CU, 16-row tiles
-  // split over 4 K groups.
+  // with 128-byte slices run six to a CU.  Up to 16 rows per CU, 16-row tiles
+  // split over 8 K groups (against 4 groups of 256-byte slices, 8 tokens:
+  // 4096 x 4096 6.35 and 6.89 us, 4096 x 16384 15.9 and 18.1, 2048 x 8192 7.4
+  // and 9.5, 768 x 768 equal); over 4 where decode16_rows16 evens the CUs out.
   // 17-64 tokens: the tile height and split from decode_plan, the tile
   // configuration from decode_tiles.
   const int64_t cus = device_cus();
@@ -822,10 +828,12 @@ hipError_t launch_qgemm_decode(const int8_t *Xq, const int8_t *Wq, const float *
   }
   if (M <= 16) {
     if (N <= 16 * cus)
-      return launch_decode<1, 1, 4, 1, 256, 4>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, packed, st);
+      return launch_decode_t<1, 1, 8, 1, 512, 4, false>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, st);
     if (N <= 32 * cus)
-      return launch_decode<1, 2, 4, 1, 512, 4>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, packed, st);
-    return launch_decode<1, 2, 1, 1, 128, 4>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, packed, st);
+      return launch_decode_t<1, 2, 4, 1, 512, 4, false>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, st);
+    if (decode16_rows16(N, cus))
+      return launch_decode_t<1, 1, 4, 1, 256, 4, false>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, st);
+    return launch_decode_t<1, 2, 1, 1, 128, 4, false>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, st);
   }
   // 17-64 tokens: the plan's tile height and K runs
   const DecodePlan p = decode_plan(M, N, K, cus, workspace != nullptr);

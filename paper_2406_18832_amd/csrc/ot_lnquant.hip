@@ -354,6 +354,13 @@ hipError_t launch_ln_quantize_act(const uint16_t *h, int64_t M, int64_t K, const
   // workgroup: 6 chunks and one row is 10 % faster than 8 chunks over the
   // shapes (its fewer registers keep more rows in flight per CU), the
   // fastest at 4 of them and within 9 % of the fastest at every one
+  // Where the rows leave CUs with few waves (up to four rows a CU), 3 chunks
+  // per thread: twice the threads shorten each row's chain of loads, sums and
+  // codes (512 x 5120 7.1 us against 8.9 with 6 chunks, 1024 x 5120 9.0
+  // against 10.2, 8 x 5120 3.9 against 4.5; 2048 x 5120 13.0 against 13.1,
+  // 512 x 20480 13.0 against 11.9, so up to K = 16384).
+  if (M <= 4 * (int64_t)device_cus() && K <= 16384)
+    return launch_lnq<3, 1>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
   if (K <= 6 * 8 * 1024) return launch_lnq<6, 1>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
   return launch_lnq<8, 1>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
 }

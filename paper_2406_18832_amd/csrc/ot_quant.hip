@@ -33,6 +33,7 @@ __device__ inline uint32_t pack4(int a, int b, int c, int d) {
          ((uint32_t)(d & 0xff) << 24);
 }
 
+template <int kRows>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void quantize_act_kernel(
     const uint16_t *__restrict__ x, int64_t M, int64_t K, float qa, const float *__restrict__ z,
     const float *__restrict__ inv_s, int8_t *__restrict__ Xq) {
@@ -46,19 +47,19 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void quantize_act_kernel(
     zr[4 * i + 0] = zz.x; zr[4 * i + 1] = zz.y; zr[4 * i + 2] = zz.z; zr[4 * i + 3] = zz.w;
     ir[4 * i + 0] = ii.x; ir[4 * i + 1] = ii.y; ir[4 * i + 2] = ii.z; ir[4 * i + 3] = ii.w;
   }
-  // groups of kRowsPerWave consecutive rows, one per wave at a time
+  // groups of kRows consecutive rows, one per wave at a time
   const int64_t group_step = (int64_t)gridDim.y * kWavesPerBlock;
-  for (int64_t g = (int64_t)blockIdx.y * kWavesPerBlock + threadIdx.y; g * kRowsPerWave < M;
+  for (int64_t g = (int64_t)blockIdx.y * kWavesPerBlock + threadIdx.y; g * kRows < M;
        g += group_step) {
-    const int64_t r0 = g * kRowsPerWave;
-    v4u v[kRowsPerWave];
+    const int64_t r0 = g * kRows;
+    v4u v[kRows];
 #pragma unroll
-    for (int u = 0; u < kRowsPerWave; ++u)
+    for (int u = 0; u < kRows; ++u)
       v[u] = r0 + u < M
                  ? __builtin_nontemporal_load(reinterpret_cast<const v4u *>(x + (r0 + u) * K + k0))
                  : v4u{0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int u = 0; u < kRowsPerWave; ++u) {
+    for (int u = 0; u < kRows; ++u) {
       if (r0 + u >= M) break;
       const uint32_t words[4] = {v[u][0], v[u][1], v[u][2], v[u][3]};
       int q[kChannelsPerLane];
@@ -146,21 +147,39 @@ hipError_t launch_qpt(const uint16_t *x, int64_t M, int64_t K, int qa, int8_t *X
 
 using namespace detail;
 
-hipError_t launch_quantize_act(const uint16_t *x, int64_t M, int64_t K, int qa, const float *z,
-                               const float *inv_s, int8_t *Xq, hipStream_t st) {
+template <int kRows>
+static hipError_t launch_qact(const uint16_t *x, int64_t M, int64_t K, int qa, const float *z,
+                              const float *inv_s, int8_t *Xq, hipStream_t st) {
   const int64_t chunks = K / kChannelsPerLane;
   const unsigned gx = (unsigned)((chunks + 63) / 64);
-  int64_t gy = (M + (int64_t)kWavesPerBlock * kRowsPerWave - 1) /
-               ((int64_t)kWavesPerBlock * kRowsPerWave);
+  int64_t gy = (M + (int64_t)kWavesPerBlock * kRows - 1) / ((int64_t)kWavesPerBlock * kRows);
   if (gy > 65535) gy = 65535;
   dim3 block(64, kWavesPerBlock);
-  quantize_act_kernel<<<dim3(gx, (unsigned)gy), block, 0, st>>>(x, M, K, (float)qa, z, inv_s, Xq);
+  quantize_act_kernel<kRows><<<dim3(gx, (unsigned)gy), block, 0, st>>>(x, M, K, (float)qa, z,
+                                                                       inv_s, Xq);
   return hipGetLastError();
+}
+
+hipError_t launch_quantize_act(const uint16_t *x, int64_t M, int64_t K, int qa, const float *z,
+                               const float *inv_s, int8_t *Xq, hipStream_t st) {
+  // Rows per wave: 8 where that leaves four waves per CU, else 2, else 1 (the
+  // rows of a wave are one after another: 512 x 5120 3.8 us with 8, 3.2 with 1
+  // or 2; 64 x 5120 3.5 and 2.9, a launch's own time).
+  const int64_t row_waves = M * ((K / kChannelsPerLane + 63) / 64);
+  const int64_t enough = 4 * (int64_t)device_cus();
+  if (row_waves >= 8 * enough)
+    return launch_qact<kRowsPerWave>(x, M, K, qa, z, inv_s, Xq, st);
+  if (row_waves >= 2 * enough) return launch_qact<2>(x, M, K, qa, z, inv_s, Xq, st);
+  return launch_qact<1>(x, M, K, qa, z, inv_s, Xq, st);
 }
 
 hipError_t launch_quantize_act_per_token(const uint16_t *x, int64_t M, int64_t K, int qa,
                                          int8_t *Xq, float *sX, hipStream_t st) {
-  if (K <= 4096) return launch_qpt<4, 1024>(x, M, K, qa, Xq, sX, st);
+  // 3 chunks of 8 channels per thread as long as a workgroup of 1024 threads
+  // holds the row: more threads per row shorten its chain of loads, maxima and
+  // codes (512 x 5120 3.4 us against 3.9 with 8 chunks, 4096 x 5120 11.6
+  // against 12.2, 8 x 20480 4.0 against 4.5, 4096 x 20480 45.8 against 48.5)
+  if (K <= 3 * 8 * 1024) return launch_qpt<3, 1024>(x, M, K, qa, Xq, sX, st);
   return launch_qpt<8, 1024>(x, M, K, qa, Xq, sX, st);
 }
 

@@ -1,4 +1,5 @@
-"""Builds libot.so (all HIP sources under csrc/) in place, for gfx950 only.
+"""Builds libot.so (all HIP sources under csrc/) in place, for gfx950 only, and
+_otbind.so (csrc/ot_bind.cpp, the Python binding's argument marshalling).
 
 Flags:
   -ffp-contract=off  the method's roundings are specified step by step; a
@@ -24,6 +25,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libot.so")
+BIND_SOURCE = os.path.join(CSRC, "ot_bind.cpp")
+BIND = os.path.join(HERE, "_otbind.so")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -114,5 +117,33 @@ def build(verbose: bool = False, extra_flags=(), sanitize: bool = False, out: st
     return lib
 
 
+def build_bind(verbose: bool = False) -> str:
+    """Compiles csrc/ot_bind.cpp (the binding's argument marshalling, host code
+    against torch's C++ headers) into _otbind.so next to this file and returns
+    its path.  Always recompiles."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cxx = os.environ.get("CXX") or shutil.which("g++") or "c++"
+    tmp = BIND + ".tmp"
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], BIND_SOURCE,
+           "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath," + os.path.join(root, "lib"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        sys.stderr.write(res.stdout + res.stderr)
+        raise RuntimeError(f"{cxx} failed with status {res.returncode}")
+    os.replace(tmp, BIND)
+    return BIND
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_bind(verbose=True))

@@ -7,12 +7,17 @@ The names match the C entry points.  Outputs are caller-allocated, as in C.
 The library is loaded on first use: ``libot.so`` next to this file, or the
 build named by the environment variable OT_LIBRARY (e.g. a sanitizer build).
 If it has not been built the first call raises: there is no fallback.
+
+The runtime entry points check and marshal their arguments in _otbind.so
+(csrc/ot_bind.cpp); where an argument is not exactly what it expects, the
+Python checks here run instead and name the fault or convert the argument.
 """
 from __future__ import annotations
 
 import ctypes
 import os
 import re
+from functools import partial
 
 import torch
 
@@ -23,6 +28,41 @@ HEADER = os.path.join(os.path.dirname(HERE), "include", "ot.h")
 OT_OK, OT_EINVAL, OT_ESHAPE, OT_ERANGE, OT_ENONFINITE, OT_EHIP, OT_ENOSCRATCH = range(7)
 
 _lib = None
+
+
+def _unbound(*args):
+    """Stands for each native marshalling function until the library is loaded."""
+    return None
+
+
+# (name in _otbind) -> the addresses its functions take first
+_BOUND = {
+    "quantize_act": ("ot_quantize_act",),
+    "quantize_act_per_token": ("ot_quantize_act_per_token",),
+    "ln_quantize_act": ("ot_ln_quantize_act",),
+    "qlinear": ("ot_qlinear", "ot_qlinear_workspace_size"),
+    "qlinear_noalloc": ("ot_qlinear_noalloc",),
+    "qlinear_packed": ("ot_qlinear_packed", "ot_qlinear_workspace_size",
+                       "ot_packed_weights_size"),
+    "qlinear_per_token": ("ot_qlinear_per_token", "ot_qlinear_workspace_size"),
+    "qlinear_asym": ("ot_qlinear_asym", "ot_qlinear_workspace_size"),
+}
+_n_quantize_act = _n_quantize_act_per_token = _n_ln_quantize_act = _unbound
+_n_qlinear = _n_qlinear_noalloc = _n_qlinear_packed = _unbound
+_n_qlinear_per_token = _n_qlinear_asym = _unbound
+
+
+def _load_bind(L) -> None:
+    """Binds the native marshalling functions to the loaded library."""
+    try:
+        from . import _otbind
+    except ImportError as e:
+        raise RuntimeError(f"{os.path.join(HERE, '_otbind.so')} cannot be loaded ({e}): build it "
+                           "with __graft_entry__.build()") from e
+    _otbind.set_current_stream(_current_stream)
+    for name, symbols in _BOUND.items():
+        addresses = [ctypes.cast(getattr(L, s), ctypes.c_void_p).value for s in symbols]
+        globals()["_n_" + name] = partial(getattr(_otbind, name), *addresses)
 
 
 class OTError(RuntimeError):
@@ -84,6 +124,7 @@ def lib() -> ctypes.CDLL:
         L.ot_pack_weights.argtypes = [vp, i64, i64, vp, vp]
         L.ot_qlinear_packed.restype = c_int
         L.ot_qlinear_packed.argtypes = [vp, vp, vp, vp, i64, i64, i64, c_int, c_int, vp, vp, vp, vp]
+        _load_bind(L)
         _lib = L
     return _lib
 
@@ -158,11 +199,15 @@ _raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
+def _current_stream():
+    if _raw_current_stream is not None and _current_device is not None:
+        return _raw_current_stream(_current_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
 def _stream(stream):
     if stream is None:
-        if _raw_current_stream is not None and _current_device is not None:
-            return _raw_current_stream(_current_device())
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -194,6 +239,9 @@ def ot_fold_weights(W, b, w_bits, z, s, Wq, sW, bprime, stream=None):
 
 def ot_quantize_act(x, a_bits, z, inv_s, Xq, stream=None):
     """x [M, K] fp16 -> Xq [M, K] int8.  Asynchronous."""
+    rc = _n_quantize_act(x, a_bits, z, inv_s, Xq, stream)
+    if rc is not None:
+        return _check(rc, "ot_quantize_act")
     M, K = x.shape
     rc = lib().ot_quantize_act(_dev(x, torch.float16, "x"), M, K, int(a_bits),
                                _dev(z, torch.float32, "z", (K,)),
@@ -205,6 +253,9 @@ def ot_quantize_act(x, a_bits, z, inv_s, Xq, stream=None):
 def ot_ln_quantize_act(h, gamma, beta, eps, a_bits, z, inv_s, Xq, stream=None):
     """h [M, K] fp16 LayerNorm input -> Xq [M, K] int8 codes of the symmetrized
     LayerNorm output.  Asynchronous."""
+    rc = _n_ln_quantize_act(h, gamma, beta, eps, a_bits, z, inv_s, Xq, stream)
+    if rc is not None:
+        return _check(rc, "ot_ln_quantize_act")
     M, K = h.shape
     rc = lib().ot_ln_quantize_act(_dev(h, torch.float16, "h"), M, K,
                                   _dev(gamma, torch.float16, "gamma", (K,)),
@@ -218,6 +269,9 @@ def ot_ln_quantize_act(h, gamma, beta, eps, a_bits, z, inv_s, Xq, stream=None):
 def ot_qlinear(Xq, Wq, sW, bprime, a_bits, w_bits, Y, acc_out=None, workspace=None, stream=None):
     """Xq [M, K] int8, Wq [N, K] int8 -> Y [M, N] fp16 (and acc_out [M, N]
     int32 if given).  Asynchronous."""
+    rc = _n_qlinear(Xq, Wq, sW, bprime, a_bits, w_bits, Y, acc_out, workspace, stream)
+    if rc is not None:
+        return _check(rc, "ot_qlinear")
     M, K = Xq.shape
     N = Wq.shape[0]
     if Wq.shape[1] != K:
@@ -234,6 +288,9 @@ def ot_qlinear(Xq, Wq, sW, bprime, a_bits, w_bits, Y, acc_out=None, workspace=No
 def ot_qlinear_noalloc(Xq, Wq, sW, bprime, a_bits, w_bits, Y, acc_out=None, stream=None):
     """ot_qlinear with the split-K scratch in the library's fixed device
     array (no workspace, no allocation).  Asynchronous."""
+    rc = _n_qlinear_noalloc(Xq, Wq, sW, bprime, a_bits, w_bits, Y, acc_out, stream)
+    if rc is not None:
+        return _check(rc, "ot_qlinear_noalloc")
     M, K = Xq.shape
     N = Wq.shape[0]
     if Wq.shape[1] != K:
@@ -277,6 +334,10 @@ def ot_qlinear_packed(Xq, Wp, N, sW, bprime, a_bits, w_bits, Y, acc_out=None, wo
                       stream=None):
     """ot_qlinear for M <= 64 with packed weights Wp (of N output channels)
     from ot_pack_weights.  Asynchronous."""
+    rc = _n_qlinear_packed(Xq, Wp, N, sW, bprime, a_bits, w_bits, Y, acc_out, workspace,
+                           stream)
+    if rc is not None:
+        return _check(rc, "ot_qlinear_packed")
     M, K = Xq.shape
     rc = lib().ot_qlinear_packed(_dev(Xq, torch.int8, "Xq"),
                                  _dev(Wp, torch.int8, "Wp", (ot_packed_weights_size(N, K),)),
@@ -313,6 +374,9 @@ def scales_from_minmax(minmax, a_bits, symmetrize=True):
 def ot_quantize_act_per_token(x, a_bits, Xq, sX, stream=None):
     """x [M, K] fp16 -> Xq [M, K] int8 and per-token scales sX [M] fp32
     (Eq. (c)).  Asynchronous."""
+    rc = _n_quantize_act_per_token(x, a_bits, Xq, sX, stream)
+    if rc is not None:
+        return _check(rc, "ot_quantize_act_per_token")
     M, K = x.shape
     rc = lib().ot_quantize_act_per_token(_dev(x, torch.float16, "x"), M, K, int(a_bits),
                                          _dev(Xq, torch.int8, "Xq", (M, K)),
@@ -338,6 +402,10 @@ def ot_qlinear_per_token(Xq, Wq, sX, sW, bprime, a_bits, w_bits, Y, acc_out=None
                          stream=None):
     """Eq. (c): Xq [M, K], Wq [N, K] int8, sX [M], sW [N], bprime [N] fp32 ->
     Y [M, N] fp16 (and acc_out [M, N] int32 if given).  Asynchronous."""
+    rc = _n_qlinear_per_token(Xq, Wq, sX, sW, bprime, a_bits, w_bits, Y, acc_out, workspace,
+                              stream)
+    if rc is not None:
+        return _check(rc, "ot_qlinear_per_token")
     M, K = Xq.shape
     N = Wq.shape[0]
     if Wq.shape[1] != K:
@@ -372,6 +440,10 @@ def ot_qlinear_asym(Xq, Wq, sW, zW, bprime, a_bits, w_bits, Y, acc_out=None, wor
                     stream=None):
     """Quantized linear with asymmetric weights: acc = Xq (Wq - zW)^T, then
     the per-channel epilogue.  Asynchronous."""
+    rc = _n_qlinear_asym(Xq, Wq, sW, zW, bprime, a_bits, w_bits, Y, acc_out, workspace,
+                         stream)
+    if rc is not None:
+        return _check(rc, "ot_qlinear_asym")
     M, K = Xq.shape
     N = Wq.shape[0]
     if Wq.shape[1] != K:

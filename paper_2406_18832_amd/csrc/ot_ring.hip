@@ -121,34 +121,50 @@ __device__ __forceinline__ void ring_body(
       make_rsrc(Wq + (int64_t)n0 * K, (uint32_t)(min(BN, N - n0) * K));
   const __amdgpu_buffer_rsrc_t rb =
       make_rsrc(Xq + (int64_t)m0 * K, (uint32_t)(min(BM, M - m0) * K));
+  // Lane i of load j fetches the chunk that belongs at stage row
+  // (j kWaves + wave) kRowsPerLoad + i / kChunks, position i mod kChunks.  The
+  // rows of a lane's loads are multiples of 16 apart, the swizzle's period, so
+  // one chunk offset serves them all.
   constexpr int kRowsPerLoad = 64 / C::kChunks;
+  static_assert(C::kWaves * kRowsPerLoad % 16 == 0, "one swizzle per lane");
+  const int row0 = wave * kRowsPerLoad + lane / C::kChunks;
+  const int gck = 16 * ((lane % C::kChunks) ^ swz_ring<C::kChunks>(row0));
   uint32_t goff[C::kLoads];
-  int gck[C::kLoads];
 #pragma unroll
   for (int j = 0; j < C::kLoads; ++j) {
-    const int row = (j * C::kWaves + wave) * kRowsPerLoad + lane / C::kChunks;
-    const int ch = (lane % C::kChunks) ^ swz_ring<C::kChunks>(row);
-    gck[j] = ch * 16;
-    goff[j] = (uint32_t)((row < BN ? row : row - BN) * K + ch * 16);
+    const int row = row0 + j * C::kWaves * kRowsPerLoad;
+    goff[j] = (uint32_t)((row < BN ? row : row - BN) * K + gck);
   }
   const int KT = (K + BK - 1) / BK;
   const int phi = (tm + tn) & 1;  // neighbouring tiles walk K one tile apart
-  // Load j of K tile kt; past the last K tile every lane is out of range
-  // (zeros into a stage nobody multiplies).
-  auto issue_one = [&](int kt, int j) {
-    int kr = kt;
-    if (kt < KT) {
-      kr = kt + phi;
-      if (kr >= KT) kr -= KT;
-    }
+  // The tile being loaded: its number, what it adds to a lane's offsets (its
+  // first K byte, or out of range past the end of K: zeros) and its stage.
+  // Worked out once per tile: with the address arithmetic at each load the K
+  // loop spends issue slots that its MFMAs and loads need (OPT-6.7B asymmetric
+  // block at 2048 tokens 457.8 -> 450.1 us, 131 x 6150 linear 19.3 -> 19.0).
+  int l_kt = 0;
+  uint32_t l_add = 0;
+  int8_t *l_dst = smem + wave * 1024;
+  int l_slot = 0;
+  auto aim = [&]() {  // l_add for tile l_kt
+    int kr = l_kt + phi;
+    if (kr >= KT) kr -= KT;
     const int k0 = kr * BK;
+    l_add = l_kt < KT && k0 + gck < K ? (uint32_t)k0 : kOobOffset;
+  };
+  auto next_tile = [&]() {
+    ++l_kt;
+    l_slot = l_slot + 1 == S ? 0 : l_slot + 1;
+    l_dst = smem + l_slot * C::kStage + wave * 1024;
+    aim();
+  };
+  auto issue_one = [&](int j) {
     const int q = j * C::kWaves + wave;  // 1 KiB block of the stage (wave-uniform)
-    int8_t *dst = smem + (kt % S) * C::kStage + q * 1024;
-    const uint32_t off = k0 + gck[j] < K ? goff[j] + (uint32_t)k0 : kOobOffset;
+    int8_t *dst = l_dst + j * C::kWaves * 1024;
     if ((j + 1) * C::kWaves <= C::kBlocksA || (j * C::kWaves < C::kBlocksA && q < C::kBlocksA))
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)dst, 16, off, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void *)dst, 16, goff[j] + l_add, 0, 0, 0);
     else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void *)dst, 16, off, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_void *)dst, 16, goff[j] + l_add, 0, 0, 0);
   };
 
   // ---- LDS -> register fragments ---------------------------------------------
@@ -180,10 +196,9 @@ __device__ __forceinline__ void ring_body(
     const int n = (u * C::kLoads + kSlots - 1) / kSlots;
     return n < C::kLoads ? n : C::kLoads;
   };
-  // One K step: MFMAs on fragment buffer cb, reads of tile rkt's step rstep
-  // into buffer nb, tile lt's loads from slot u0 on.
-  auto kstep = [&](int cb, int step, int rkt, int rstep, int nb, int lt, int u0) {
-    const int8_t *st = smem + (rkt % S) * C::kStage;
+  // One K step: MFMAs on fragment buffer cb, reads of step rstep of the tile in
+  // stage st into buffer nb, the aimed tile's loads from slot u0 on.
+  auto kstep = [&](int cb, int step, const int8_t *st, int rstep, int nb, int u0) {
     constexpr int kN = kMfma > kReads ? kMfma : kReads;
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
@@ -197,7 +212,7 @@ __device__ __forceinline__ void ring_body(
         acc[f][g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[cb][f], fb[cb][g], acc[f][g], 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < C::kLoads; ++j)
-          if (j >= upto(u0 + i) && j < upto(u0 + i + 1)) issue_one(lt, j);
+          if (j >= upto(u0 + i) && j < upto(u0 + i + 1)) issue_one(j);
       }
     }
     if constexpr (EPI == kEpiAsym) {
@@ -221,27 +236,34 @@ __device__ __forceinline__ void ring_body(
   };
 
   // ---- main loop (the waits and the barrier as in the large tiles) -------------
+  aim();
 #pragma unroll
-  for (int t = 0; t < S - 1; ++t)
+  for (int t = 0; t < S - 1; ++t) {
 #pragma unroll
-    for (int j = 0; j < C::kLoads; ++j) issue_one(t, j);
+    for (int j = 0; j < C::kLoads; ++j) issue_one(j);
+    next_tile();
+  }
   wait_vmcnt<(S - 2) * C::kLoads>();  // K tile 0 (and the parameters) have landed
   lds_barrier();
   // keeps the compiler from sinking the parameter loads past the loop
   asm volatile("" : "+v"(p_s), "+v"(p_b), "+v"(p_x), "+v"(p_z));
 #pragma unroll
   for (int j = 0; j < C::kLoads; ++j)
-    if (j < upto(kMfma)) issue_one(S - 1, j);
+    if (j < upto(kMfma)) issue_one(j);
 #pragma unroll
   for (int f = 0; f < C::kFN; ++f)
     fa[0][f] = *reinterpret_cast<const v4i *>(smem + a_base + f * 32 * BK + frag_off[0]);
 #pragma unroll
   for (int g = 0; g < C::kFM; ++g)
     fb[0][g] = *reinterpret_cast<const v4i *>(smem + b_base + g * 32 * BK + frag_off[0]);
+  int r_slot = 0;  // stage of tile kt
   for (int kt = 0; kt < KT; ++kt) {
+    const int8_t *st = smem + r_slot * C::kStage;
 #pragma unroll
     for (int s = 0; s + 1 < C::kSteps; ++s)
-      kstep(s & 1, s, kt, s + 1, (s + 1) & 1, kt + S - 1, kMfma * (s + 1));
+      kstep(s & 1, s, st, s + 1, (s + 1) & 1, kMfma * (s + 1));
+    r_slot = r_slot + 1 == S ? 0 : r_slot + 1;
+    next_tile();
     // this wave's reads of tile kt are done once lgkmcnt drains, tile kt+1 has
     // landed once at most S-2 younger tiles are in flight; after the barrier
     // tile kt's stage takes tile kt+S
@@ -249,7 +271,7 @@ __device__ __forceinline__ void ring_body(
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
     wait_vmcnt<(S - 2) * C::kLoads>();
     lds_barrier();
-    kstep(1, C::kSteps - 1, kt + 1, 0, 0, kt + S, 0);
+    kstep(1, C::kSteps - 1, smem + r_slot * C::kStage, 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   }
   wait_vmcnt<0>();                     // the trailing out-of-range loads

@@ -54,11 +54,16 @@ class StatusWord {
     }
   }
   // Only when no kernel that may write it still runs (its stream has been
-  // synchronized, or nothing was launched): any other word is never handed
-  // out again.
+  // synchronized): any other word is never handed out again.
   void release() {
     if (word_ != nullptr) used_.fetch_and(~(uint64_t(1) << index_), std::memory_order_release);
     word_ = nullptr;
+  }
+  // After a launch that reported an error.  The error may be an older one of
+  // this thread and the kernel running all the same: the word goes back only
+  // once the stream is known to be idle.
+  void release_after_error(hipStream_t st) {
+    if (word_ != nullptr && hipStreamSynchronize(st) == hipSuccess) release();
   }
   int *word() const { return word_; }
   bool raised() const { return __atomic_load_n(word_, __ATOMIC_ACQUIRE) != 0; }
@@ -140,7 +145,7 @@ ot_status ot_calibrate(const uint16_t *x, int64_t rows, int64_t K, int a_bits, i
     if (status.word() != nullptr) {
       if (ot::launch_calib_finish(minmax, K, qmax(a_bits), z, s, inv_s, status.word(), st) !=
           hipSuccess) {
-        status.release();  // it was not launched
+        status.release_after_error(st);
         return OT_EHIP;
       }
       if (hipStreamSynchronize(st) != hipSuccess) return OT_EHIP;
@@ -176,7 +181,7 @@ ot_status ot_scales_from_minmax(const float *minmax, int64_t K, int a_bits, int 
 static ot_status fold_result(hipError_t e, StatusWord &status, const float *sW,
                              const float *bprime, int64_t N, hipStream_t st) {
   if (e != hipSuccess) {
-    status.release();  // nothing was launched
+    status.release_after_error(st);
     return OT_EHIP;
   }
   if (status.word() != nullptr) {

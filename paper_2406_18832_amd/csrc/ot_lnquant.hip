@@ -347,19 +347,38 @@ using namespace detail;
 hipError_t launch_ln_quantize_act(const uint16_t *h, int64_t M, int64_t K, const uint16_t *gamma,
                                   const uint16_t *beta, float eps, int qa, const float *z,
                                   const float *inv_s, int8_t *Xq, hipStream_t st) {
-  // one row per workgroup, 6 chunks of 8 channels per thread up to
+  // Two rows per workgroup for wide rows and many of them (140000 elements per
+  // CU: 36 M on 256 CUs).  A row reads 12 bytes of parameters from the L2 per
+  // channel beside its own 2, and two rows share them; each thread's chunks are
+  // as many as let a workgroup of 4 waves (8 past K = 16384) hold the rows, so
+  // that few threads idle in the last chunk.  Against one row and 6 chunks per
+  // thread: 8192 x 7168 50.6 and 60.7 us, 4096 x 9216 32.7 and 38.3, 8000 x
+  // 14336 87.1 and 109.3, 3333 x 20480 63.3 and 69.6, 3200 x 12288 36.4 and
+  // 39.3.  With fewer elements the fewer workgroups leave waves missing (3100 x
+  // 10240 30.1 and 29.8, 1100 x 16400 23.5 and 21.0), with narrower rows they
+  // do not pay (8192 x 4096 31.4 and 30.2, 4096 x 5120 22.2 and 22.0).
+  const int64_t cus = device_cus();
+  if (K > 6144 && K <= 32768 && M * K >= 140000 * cus) {
+    const int64_t waves = K <= 16384 ? 4 : 8;
+    switch ((K / 8 + waves * 64 - 1) / (waves * 64)) {
+      case 4: return launch_lnq<4, 2>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
+      case 5: return launch_lnq<5, 2>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
+      case 6: return launch_lnq<6, 2>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
+      case 7: return launch_lnq<7, 2>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
+      default: return launch_lnq<8, 2>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
+    }
+  }
+  // Fewer: one row per workgroup, 6 chunks of 8 channels per thread up to
   // K = 49152 (a workgroup of at most 1024 threads) and 8 beyond (up to
   // K = 65536).  Measured on 8 shapes (K = 2048 ... 12288, 1024 to 8192
-  // rows) against 3 to 8 chunks per thread and 1, 2 or 4 rows per
-  // workgroup: 6 chunks and one row is 10 % faster than 8 chunks over the
-  // shapes (its fewer registers keep more rows in flight per CU), the
-  // fastest at 4 of them and within 9 % of the fastest at every one
+  // rows) against 3 to 8 chunks per thread: 6 chunks is 10 % faster than 8
+  // over the shapes (its fewer registers keep more rows in flight per CU).
   // Where the rows leave CUs with few waves (up to four rows a CU), 3 chunks
   // per thread: twice the threads shorten each row's chain of loads, sums and
   // codes (512 x 5120 7.1 us against 8.9 with 6 chunks, 1024 x 5120 9.0
   // against 10.2, 8 x 5120 3.9 against 4.5; 2048 x 5120 13.0 against 13.1,
   // 512 x 20480 13.0 against 11.9, so up to K = 16384).
-  if (M <= 4 * (int64_t)device_cus() && K <= 16384)
+  if (M <= 4 * cus && K <= 16384)
     return launch_lnq<3, 1>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
   if (K <= 6 * 8 * 1024) return launch_lnq<6, 1>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);
   return launch_lnq<8, 1>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);

@@ -356,9 +356,12 @@ hipError_t launch_ln_quantize_act(const uint16_t *h, int64_t M, int64_t K, const
   // 14336 87.1 and 109.3, 3333 x 20480 63.3 and 69.6, 3200 x 12288 36.4 and
   // 39.3.  With fewer elements the fewer workgroups leave waves missing (3100 x
   // 10240 30.1 and 29.8, 1100 x 16400 23.5 and 21.0), with narrower rows they
-  // do not pay (8192 x 4096 31.4 and 30.2, 4096 x 5120 22.2 and 22.0).
+  // do not pay (8192 x 4096 31.4 and 30.2, 4096 x 5120 22.2 and 22.0), nor just
+  // past 16384, where 8 waves' last chunk is mostly empty (2200 x 16400 37.5 and
+  // 36.5; 1800 x 20512 36.6 and 37.0, 1460 x 24592 34.2 and 44.2).
   const int64_t cus = device_cus();
-  if (K > 6144 && K <= 32768 && M * K >= 140000 * cus) {
+  const bool wide = (K > 6144 && K <= 16384) || (K >= 18432 && K <= 32768);
+  if (wide && M * K >= 140000 * cus) {
     const int64_t waves = K <= 16384 ? 4 : 8;
     switch ((K / 8 + waves * 64 - 1) / (waves * 64)) {
       case 4: return launch_lnq<4, 2>(h, M, K, gamma, beta, eps, qa, z, inv_s, Xq, st);

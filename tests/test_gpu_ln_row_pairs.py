@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 # one width per chunk count and workgroup size, whole and ragged against the
 # threads, the narrowest and the widest; an odd number of rows throughout
-@pytest.mark.parametrize("K", [6160, 8192, 8208, 12288, 12304, 16384, 16400, 20480, 24560,
-                               28672, 32768])
+@pytest.mark.parametrize("K", [6160, 8192, 8208, 12288, 12304, 16384, 16400, 18432, 20480,
+                               24560, 28672, 32768])
 def test_row_pairs_match_single_rows(K):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     M = -(-140000 * cus // K) | 1

@@ -142,8 +142,9 @@ PyObject *run(PyObject *const *a, Py_ssize_t n, Py_ssize_t want, Body body) {
   int rc = 0;
   try {
     rc = body(args);
-  } catch (...) {  // a tensor without storage, e.g. under tracing
+  } catch (...) {  // a tensor without storage (under tracing, say) or one that raised
     args.ok = false;
+    PyErr_Clear();  // ot.py asks the tensor again and lets its error through
   }
   if (!args.ok) Py_RETURN_NONE;
   return PyLong_FromLong(rc);

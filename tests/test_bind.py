@@ -142,3 +142,29 @@ def test_streams_and_statuses_pass_through():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(args[6].cpu(), want[6])
+
+
+class _Wrapper(torch.Tensor):
+    """A wrapper subclass that answers for its own layout, with an error."""
+
+    @staticmethod
+    def __new__(cls, *shape):
+        return torch.Tensor._make_wrapper_subclass(
+            cls, shape, dtype=torch.float16, device="cuda", dispatch_sizes_strides_policy="strides")
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise LookupError(f"this tensor has no {func}")
+
+
+def test_an_error_raised_by_a_tensor_is_the_callers():
+    """A tensor that raises from Python while it is looked at: its own error
+    reaches the caller, and none is left behind by the native checks."""
+    ot.lib()
+    x = _Wrapper(M, K)
+    with pytest.raises(LookupError, match="this tensor has no"):
+        x.is_contiguous()
+    _, call, args = _entry("quantize_act", "cpu")
+    assert ot._n_quantize_act(x, *args[1:], 0) is None
+    with pytest.raises(LookupError, match="this tensor has no"):
+        call(x, *args[1:])

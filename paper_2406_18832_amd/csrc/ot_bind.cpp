@@ -25,8 +25,11 @@ struct Args {
   PyObject *const *a;
   bool ok = true;
 
+  // Plain tensors (and parameters) only, by their type: an object can claim to
+  // be a tensor (its __class__) without a tensor's memory, and a subclass may
+  // answer for itself, which only the Python checks ask it to.
   const at::Tensor *tensor(int i, at::ScalarType type) {
-    if (!ok || !THPVariable_Check(a[i])) return fail();
+    if (!ok || !THPVariable_CheckExact(a[i])) return fail();
     const at::Tensor &t = THPVariable_Unpack(a[i]);
     if (t.scalar_type() != type || !t.is_cuda() || !t.is_contiguous()) return fail();
     return &t;

@@ -168,3 +168,44 @@ def test_an_error_raised_by_a_tensor_is_the_callers():
     assert ot._n_quantize_act(x, *args[1:], 0) is None
     with pytest.raises(LookupError, match="this tensor has no"):
         call(x, *args[1:])
+
+
+_LIAR = """
+import sys, types
+sys.path.insert(0, {root!r})
+import torch
+from paper_2406_18832_amd import ot
+
+class Liar:
+    __class__ = torch.Tensor      # what unittest.mock's specced objects do
+
+class Own(torch.Tensor):          # answers for itself, as a plain tensor's methods do not
+    @classmethod
+    def __torch_function__(cls, func, types, args=(), kwargs=None):
+        raise LookupError("its own answer")
+
+ot.lib()
+args = [8, torch.zeros(48), torch.zeros(48), torch.zeros(5, 48, dtype=torch.int8)]
+assert isinstance(Liar(), torch.Tensor)
+assert ot._n_quantize_act(Liar(), *args, 0) is None
+x = torch.zeros(5, 48, dtype=torch.float16).as_subclass(Own)
+assert ot._n_quantize_act(x, *args, 0) is None
+try:
+    ot.ot_quantize_act(x, *args)
+except LookupError as e:
+    print("passed", e)
+"""
+
+
+def test_only_plain_tensors_are_taken_natively():
+    """An object that only claims to be a tensor has none of a tensor's memory
+    to look at, and a subclass may answer for itself: both are left to the
+    Python checks (in a process of its own: reading the first is undefined)."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", _LIAR.format(root=root)], capture_output=True,
+                         text=True, timeout=300)
+    assert run.returncode == 0 and "passed its own answer" in run.stdout, (run.returncode, run.stdout,
+                                                                         run.stderr[-2000:])

@@ -536,22 +536,22 @@ static double prefill_cost(int64_t M, int64_t N, int64_t K, int bn, int bm, int6
 // large tiles and the two-stage 256 x 128 tile that served these launches
 // before were 93 % over it on the first 90 of them.
 struct PrefillTile {
-  int bn, bm;
+  int bn, bm, threads;
   float once, pass, per_k;
   const char *name;
 };
 static const PrefillTile kPrefillTiles[] = {
-    {256, 256, -4.60f, 11.41f, 12.29f, "prefill 256x256"},
-    {320, 256, -3.41f, 15.61f, 14.14f, "prefill 320x256"},
-    {192, 256, -3.09f, 9.89f, 10.70f, "prefill 192x256"},
-    {256, 128, -2.49f, 8.73f, 7.32f, "prefill 256x128"},
-    {192, 128, -1.38f, 7.86f, 5.84f, "prefill 192x128"},
-    {128, 128, -0.38f, 5.55f, 4.38f, "prefill 128x128"},
-    {128, 96, 0.44f, 5.73f, 3.84f, "prefill 128x96"},
-    {64, 128, 0.25f, 4.47f, 2.72f, "prefill 64x128"},
-    {64, 64, 0.48f, 3.81f, 1.87f, "prefill 64x64"},
-    {32, 64, 1.21f, 3.08f, 1.38f, "prefill 32x64"},
-    {32, 32, 1.24f, 2.72f, 0.97f, "prefill 32x32"},
+    {256, 256, 512, -4.60f, 11.41f, 12.29f, "prefill 256x256"},
+    {320, 256, 512, -3.41f, 15.61f, 14.14f, "prefill 320x256"},
+    {192, 256, 512, -3.09f, 9.89f, 10.70f, "prefill 192x256"},
+    {256, 128, 512, -2.49f, 8.73f, 7.32f, "prefill 256x128"},
+    {192, 128, 512, -1.38f, 7.86f, 5.84f, "prefill 192x128"},
+    {128, 128, 512, -0.38f, 5.55f, 4.38f, "prefill 128x128"},
+    {128, 96, 256, 0.44f, 5.73f, 3.84f, "prefill 128x96"},
+    {64, 128, 512, 0.25f, 4.47f, 2.72f, "prefill 64x128"},
+    {64, 64, 256, 0.48f, 3.81f, 1.87f, "prefill 64x64"},
+    {32, 64, 256, 1.21f, 3.08f, 1.38f, "prefill 32x64"},
+    {32, 32, 256, 1.24f, 2.72f, 0.97f, "prefill 32x32"},
 };
 constexpr int kLargeTiles = 3;  // the first ones: this file's
 constexpr int k256x128 = 3;
@@ -562,6 +562,9 @@ static const PrefillTile &prefill_tile(int64_t M, int64_t N, int64_t K) {
   // 1000 channels, K = 1040: 9.5 us against 6 on 32 x 64).
   if (M > 256 && M <= 384 && N > 768 && N <= 1024 && K <= 1040) return kPrefillTiles[k256x128];
   const int64_t cus = device_cus();
+  auto tiles = [&](const PrefillTile &t) {
+    return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  };
   const PrefillTile *large = &kPrefillTiles[0];
   double large_cost = prefill_cost(M, N, K, large->bn, large->bm, cus);
   for (int i = 1; i < kLargeTiles; ++i) {
@@ -575,9 +578,10 @@ static const PrefillTile &prefill_tile(int64_t M, int64_t N, int64_t K) {
   double best_t = 0;
   for (const PrefillTile &t : kPrefillTiles) {
     if (t.bm == 256 && &t != large) continue;
-    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-    if (tiles > INT32_MAX) continue;  // the grid is a 32-bit count
-    const double passes = (double)((tiles + cus - 1) / cus);
+    // a launch takes fewer than 2^32 work-items: of hundreds of millions of
+    // tokens by few channels, the ring tiles would have more
+    if (t.bm != 256 && tiles(t) * t.threads > UINT32_MAX) continue;
+    const double passes = (double)((tiles(t) + cus - 1) / cus);
     const double us = t.once + passes * (t.pass + t.per_k * 1e-3 * (double)K);
     if (best == nullptr || us < best_t) {
       best = &t;

@@ -1,0 +1,79 @@
+"""Grids and workgroups that the entry points launch, without a GPU: the launch
+configurations that the library hands to the HIP runtime are recorded and the
+launches left out (a preloaded library), in a process of its own.  256 CUs, as
+on MI355X, without a device."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from paper_2406_18832_amd import ot
+
+RECORDER = r"""
+#include <stddef.h>
+#include <stdint.h>
+struct dim3 { uint32_t x, y, z; };
+extern "C" {
+uint64_t ot_test_grid[3], ot_test_block[3], ot_test_launches;
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t, void *) {
+  ot_test_grid[0] = g.x; ot_test_grid[1] = g.y; ot_test_grid[2] = g.z;
+  ot_test_block[0] = b.x; ot_test_block[1] = b.y; ot_test_block[2] = b.z;
+  ++ot_test_launches;
+  return 1;  // nonzero: the launch is left out
+}
+}
+"""
+
+CALLER = r"""
+import ctypes, sys
+R, L = ctypes.CDLL(sys.argv[1]), ctypes.CDLL(sys.argv[2])
+grid, block = ((ctypes.c_uint64 * 3).in_dll(R, n) for n in ("ot_test_grid", "ot_test_block"))
+launches = ctypes.c_uint64.in_dll(R, "ot_test_launches")
+vp, i64, ci, P = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, 4096   # P: aligned, never read
+for line in sys.stdin:
+    name, M, N, K = line.split()
+    M, N, K = int(M), int(N), int(K)
+    launches.value = 0
+    if name == "qlinear":
+        L.ot_qlinear(vp(P), vp(P), vp(P), vp(P), i64(M), i64(N), i64(K), ci(8), ci(8), vp(P), None, None, None)
+    else:
+        L.ot_quantize_act_per_token(vp(P), i64(M), i64(K), ci(8), vp(P), vp(P), None)
+    print(launches.value, *grid, *block, flush=True)
+"""
+
+
+@pytest.fixture(scope="module")
+def launch(tmp_path_factory):
+    """launch([(call, M, N, K), ...]) -> (grid, block) of each call's one launch."""
+    d = tmp_path_factory.mktemp("launches")
+    src, so = d / "recorder.cpp", d / "recorder.so"
+    src.write_text(RECORDER)
+    subprocess.run([os.environ.get("CXX") or shutil.which("g++") or "c++", "-shared", "-fPIC", "-O1",
+                    str(src), "-o", str(so)], check=True)
+
+    def run(calls):
+        env = dict(os.environ, LD_PRELOAD=str(so))
+        out = subprocess.run([sys.executable, "-c", CALLER, str(so), ot.LIB_PATH], env=env,
+                             input="".join("%s %d %d %d\n" % c for c in calls), text=True,
+                             capture_output=True, timeout=300)
+        assert out.returncode == 0, out.stderr[-2000:]
+        rows = [[int(v) for v in line.split()] for line in out.stdout.splitlines()]
+        assert len(rows) == len(calls) and all(r[0] == 1 for r in rows), rows
+        return [(r[1:4], r[4:7]) for r in rows]
+    return run
+
+
+# A launch takes fewer than 2^32 work-items per dimension.  Tall calls (tokens
+# in the hundreds of millions by few channels, within 288 GB) on which the tile
+# of the least estimated time has more, and the largest of the 256-token tiles'.
+TALL = [(1 << 30, 1, 16), (1 << 30, 16, 16), (1 << 30, 33, 32), (1300000000, 64, 16),
+        (1073741825, 8, 64), (2147483391, 1, 16), (1 << 29, 16, 16), (65, 1 << 30, 16)]
+
+
+def test_prefill_grids_stay_within_the_launch_limit(launch):
+    for (M, N, K), (grid, block) in zip(TALL, launch([("qlinear", *s) for s in TALL])):
+        bn, bm = (int(v) for v in ot.ot_qlinear_plan(M, N, K).split()[1].split("x"))
+        assert grid == [-(-M // bm) * -(-N // bn), 1, 1]
+        assert grid[0] * block[0] < 1 << 32, (M, N, K, grid, block)

@@ -178,8 +178,13 @@ hipError_t launch_quantize_act_per_token(const uint16_t *x, int64_t M, int64_t K
   // 3 chunks of 8 channels per thread as long as a workgroup of 1024 threads
   // holds the row: more threads per row shorten its chain of loads, maxima and
   // codes (512 x 5120 3.4 us against 3.9 with 8 chunks, 4096 x 5120 11.6
-  // against 12.2, 8 x 20480 4.0 against 4.5, 4096 x 20480 45.8 against 48.5)
-  if (K <= 3 * 8 * 1024) return launch_qpt<3, 1024>(x, M, K, qa, Xq, sX, st);
+  // against 12.2, 8 x 20480 4.0 against 4.5, 4096 x 20480 45.8 against 48.5).
+  // A launch takes fewer than 2^32 work-items: past that (tens of millions of
+  // rows) the fewest threads per row, 4 chunks each up to K = 4096 and 8 beyond.
+  const int64_t threads = (K / 8 + 3 * 64 - 1) / (3 * 64) * 64;
+  if (K <= 3 * 8 * 1024 && M * threads <= UINT32_MAX)
+    return launch_qpt<3, 1024>(x, M, K, qa, Xq, sX, st);
+  if (K <= 4096) return launch_qpt<4, 1024>(x, M, K, qa, Xq, sX, st);
   return launch_qpt<8, 1024>(x, M, K, qa, Xq, sX, st);
 }
 

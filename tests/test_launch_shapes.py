@@ -77,3 +77,11 @@ def test_prefill_grids_stay_within_the_launch_limit(launch):
         bn, bm = (int(v) for v in ot.ot_qlinear_plan(M, N, K).split()[1].split("x"))
         assert grid == [-(-M // bm) * -(-N // bn), 1, 1]
         assert grid[0] * block[0] < 1 << 32, (M, N, K, grid, block)
+
+
+def test_per_token_quantizer_grids_stay_within_the_launch_limit(launch):
+    """One workgroup per row: tens of millions of rows, within 288 GB."""
+    sizes = [(33554432, 1552), (67108863, 2048), (22369622, 3104), (33554431, 4096), (22369622, 4112)]
+    for (M, K), (grid, block) in zip(sizes, launch([("per_token", M, 0, K) for M, K in sizes])):
+        assert grid == [M, 1, 1]
+        assert grid[0] * block[0] < 1 << 32, (M, K, grid, block)

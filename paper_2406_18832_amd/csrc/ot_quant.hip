@@ -177,13 +177,35 @@ hipError_t launch_quantize_act_per_token(const uint16_t *x, int64_t M, int64_t K
                                          int8_t *Xq, float *sX, hipStream_t st) {
   // 3 chunks of 8 channels per thread as long as a workgroup of 1024 threads
   // holds the row: more threads per row shorten its chain of loads, maxima and
-  // codes (512 x 5120 3.4 us against 3.9 with 8 chunks, 4096 x 5120 11.6
-  // against 12.2, 8 x 20480 4.0 against 4.5, 4096 x 20480 45.8 against 48.5).
-  // A launch takes fewer than 2^32 work-items: past that (tens of millions of
-  // rows) the fewest threads per row, 4 chunks each up to K = 4096 and 8 beyond.
-  const int64_t threads = (K / 8 + 3 * 64 - 1) / (3 * 64) * 64;
-  if (K <= 3 * 8 * 1024 && M * threads <= UINT32_MAX)
-    return launch_qpt<3, 1024>(x, M, K, qa, Xq, sX, st);
+  // codes (512 x 5120 3.4 us against 3.9 with 8 chunks, 256 x 20480 6.0 against
+  // 6.6, 6000 x 20480 65.6 against 69.4).  Fewer threads (4 chunks each up to
+  // K = 4096, 8 beyond) where the row fills their waves and more waves would
+  // only leave fewer rows to a CU at once; inputs from HBM, and cached:
+  //   - up to K = 4096 wherever 4 chunks need a wave fewer (6000 x 1600 8.1 us
+  //     against 8.5 with 3 chunks, cached 6.6 against 7.4; 4096 x 4096 10.7
+  //     against 11.1, cached 9.9 against 10.0);
+  //   - 8 chunks in 2 or 3 waves with at least four rows and under 156250
+  //     elements a CU (2048 x 8192 11.8 and 11.8, cached 10.3 against 10.9;
+  //     4096 x 8416 19.2 against 20.0, 2025 x 9888 13.6 against 14.1; past that line 6000 x 8192 cached 24.8
+  //     against 23.8, below it 256 x 8192 4.4 against 3.9);
+  //   - 8 chunks in 4 or, with at least seven rows a CU, 5 waves under 350000
+  //     elements a CU (2048 x 14336 16.6 against 18.4, cached 15.4 against 16.7;
+  //     4096 x 14336 29.1 against 31.0, cached 29.0 against 28.5; 3988 x 17120
+  //     34.8 against 36.4; past the line 8496 x 16304 80.2 against 72.7).
+  // A launch takes fewer than 2^32 work-items: tens of millions of rows take
+  // the fewer threads too.
+  const int64_t chunks = K / 8, threads = (chunks + 3 * 64 - 1) / (3 * 64) * 64;
+  bool three = K <= 3 * 8 * 1024 && M * threads <= UINT32_MAX;
+  if (K <= 4096) {
+    three = three && threads <= (chunks + 4 * 64 - 1) / (4 * 64) * 64;
+  } else {
+    const int64_t cus = device_cus();
+    if (K > 7680 && K <= 10240)
+      three = three && (M < 4 * cus || M * K >= 156250 * cus);
+    else if (K > 12288 && K <= 20480)
+      three = three && ((K > 16384 && M < 7 * cus) || M * K >= 350000 * cus);
+  }
+  if (three) return launch_qpt<3, 1024>(x, M, K, qa, Xq, sX, st);
   if (K <= 4096) return launch_qpt<4, 1024>(x, M, K, qa, Xq, sX, st);
   return launch_qpt<8, 1024>(x, M, K, qa, Xq, sX, st);
 }

@@ -78,6 +78,14 @@ def test_per_token_chunks_per_thread(M, K):
     assert np.array_equal(host(Xq), rq) and np.array_equal(host(sX), rs)
 
 
+# 4 chunks per thread (2048, 3088, 4096), 8 in 2, 3 and 4 waves, and beside them
+@pytest.mark.parametrize("M,K", [(3, 2048), (2, 3088), (3, 4096), (1024, 7696), (1023, 10240),
+                                 (1024, 10240), (2, 12288), (3, 12304), (2, 16384), (2, 16400),
+                                 (1792, 16400)])
+def test_per_token_fewer_threads(M, K):
+    test_per_token_chunks_per_thread(M, K)
+
+
 @pytest.mark.parametrize("M,K", [(1024, 784), (1025, 784), (2, 16384), (2, 16400)])
 def test_layernorm_chunks_per_thread(M, K):
     print(f"[case] ln M={M} K={K}", flush=True)

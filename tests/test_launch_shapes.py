@@ -85,3 +85,21 @@ def test_per_token_quantizer_grids_stay_within_the_launch_limit(launch):
     for (M, K), (grid, block) in zip(sizes, launch([("per_token", M, 0, K) for M, K in sizes])):
         assert grid == [M, 1, 1]
         assert grid[0] * block[0] < 1 << 32, (M, K, grid, block)
+
+
+# (rows, K) -> threads of a row: 3 chunks each, except where 4 need a wave fewer
+# up to K = 4096, and 8 beyond at the widths, rows and elements where their 2 to 4
+# waves measured faster (either side of each line)
+@pytest.mark.parametrize("M,K,threads", [
+    (512, 1536, 64), (512, 1552, 64), (14544, 1696, 64), (4096, 2048, 64), (4096, 2064, 128),
+    (9089, 3072, 128), (4096, 3088, 128), (8192, 4096, 128), (4096, 4112, 192), (4096, 5120, 256),
+    (4096, 7680, 320), (1023, 7696, 384), (1024, 7696, 128), (4096, 8192, 128), (5197, 7696, 128),
+    (5198, 7696, 384), (2048, 8416, 192), (1024, 10240, 192), (4000, 10256, 448),
+    (4000, 12288, 512), (4000, 12304, 256), (100, 14768, 256), (4448, 14768, 256),
+    (5468, 16384, 256), (5469, 16384, 704), (8496, 16304, 704), (1791, 16400, 704),
+    (1792, 16400, 320), (3988, 17120, 320), (4374, 20480, 320), (4375, 20480, 896),
+    (3000, 20496, 896),
+    (3000, 24576, 1024), (4, 24592, 448)])
+def test_per_token_quantizer_threads(launch, M, K, threads):
+    (grid, block), = launch([("per_token", M, 0, K)])
+    assert grid == [M, 1, 1] and block == [threads, 1, 1]

@@ -91,8 +91,9 @@ def asan_runtime() -> str:
 
 def build(verbose: bool = False, extra_flags=(), sanitize: bool = False, out: str = None) -> str:
     """Compiles every csrc/*.hip into libot.so next to this file (or into
-    out) and returns its path.  Always recompiles.  sanitize=True: host code
-    under AddressSanitizer and UndefinedBehaviorSanitizer."""
+    out) and returns its path; next to this file, with the binding's _otbind.so
+    (build_bind).  Always recompiles.  sanitize=True: host code under
+    AddressSanitizer and UndefinedBehaviorSanitizer."""
     lib = out or LIB
     tmp = lib + ".tmp"
     flags = list(HIPCC_FLAGS)
@@ -114,6 +115,8 @@ def build(verbose: bool = False, extra_flags=(), sanitize: bool = False, out: st
             if verbose:
                 print(line)
     os.replace(tmp, lib)
+    if out is None:
+        build_bind(verbose)
     return lib
 
 
@@ -146,4 +149,3 @@ def build_bind(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True))
-    print(build_bind(verbose=True))

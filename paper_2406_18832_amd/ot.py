@@ -11,12 +11,15 @@ If it has not been built the first call raises: there is no fallback.
 The runtime entry points check and marshal their arguments in _otbind.so
 (csrc/ot_bind.cpp); where an argument is not exactly what it expects, the
 Python checks here run instead and name the fault or convert the argument.
+They also run, with a warning, where _otbind.so has not been built: the kernels
+are the same, each call takes some 3 us more of host time.
 """
 from __future__ import annotations
 
 import ctypes
 import os
 import re
+import warnings
 from functools import partial
 
 import torch
@@ -53,12 +56,15 @@ _n_qlinear_per_token = _n_qlinear_asym = _unbound
 
 
 def _load_bind(L) -> None:
-    """Binds the native marshalling functions to the loaded library."""
+    """Binds the native marshalling functions to the loaded library; without
+    _otbind.so they stay unbound (the Python checks) and a warning says so."""
     try:
         from . import _otbind
     except ImportError as e:
-        raise RuntimeError(f"{os.path.join(HERE, '_otbind.so')} cannot be loaded ({e}): build it "
-                           "with __graft_entry__.build()") from e
+        warnings.warn(f"{os.path.join(HERE, '_otbind.so')} cannot be loaded ({e}): arguments are "
+                      "checked in Python, which is slower; build it with build_lib.build()",
+                      RuntimeWarning, stacklevel=3)
+        return
     _otbind.set_current_stream(_current_stream)
     for name, symbols in _BOUND.items():
         addresses = [ctypes.cast(getattr(L, s), ctypes.c_void_p).value for s in symbols]

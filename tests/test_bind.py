@@ -1,9 +1,14 @@
 """The binding's native argument marshalling (_otbind.so): it takes exactly the
 arguments that the Python checks take, and leaves every other one to them."""
+import os
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
-from paper_2406_18832_amd import ot
+from paper_2406_18832_amd import build_lib, ot
 
 M, K, N = 5, 48, 33
 
@@ -201,11 +206,63 @@ def test_only_plain_tensors_are_taken_natively():
     """An object that only claims to be a tensor has none of a tensor's memory
     to look at, and a subclass may answer for itself: both are left to the
     Python checks (in a process of its own: reading the first is undefined)."""
-    import os
-    import subprocess
-    import sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     run = subprocess.run([sys.executable, "-c", _LIAR.format(root=root)], capture_output=True,
                          text=True, timeout=300)
     assert run.returncode == 0 and "passed its own answer" in run.stdout, (run.returncode, run.stdout,
                                                                          run.stderr[-2000:])
+
+
+_BARE = """
+import sys, warnings
+sys.path.insert(0, {root!r})
+import torch
+from paper_2406_18832_amd import ot
+
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    assert ot.ot_abi_version() == 1
+print([str(w.message) for w in seen])
+assert ot.HERE.startswith({root!r}) and ot._n_qlinear is ot._unbound
+try:
+    ot.ot_quantize_act(torch.zeros(5, 48, dtype=torch.float16), 8, torch.zeros(48), torch.zeros(48),
+                       torch.zeros(5, 48, dtype=torch.int8))
+except ValueError as e:
+    print("passed", e)
+"""
+
+
+def _package_copy(tmp_path):
+    """The package's Python files alone in a folder of their own."""
+    pkg = tmp_path / "paper_2406_18832_amd"
+    shutil.copytree(ot.HERE, pkg, ignore=lambda d, names: [n for n in names if n == "csrc" or
+                                                           not n.endswith(".py")])
+    return pkg
+
+
+def _run(code, lib):
+    return subprocess.run([sys.executable, "-c", code], env=dict(os.environ, OT_LIBRARY=lib),
+                          capture_output=True, text=True, timeout=300)
+
+
+def test_a_library_without_the_binding_is_enough(tmp_path):
+    """libot.so alone serves every call, through the Python checks."""
+    _package_copy(tmp_path)
+    run = _run(_BARE.format(root=str(tmp_path)), os.path.abspath(ot.LIB_PATH))
+    assert run.returncode == 0 and "passed x must be on the GPU" in run.stdout, run.stderr[-2000:]
+    assert "arguments are checked in Python" in run.stdout
+
+
+def test_one_build_makes_library_and_binding(monkeypatch, tmp_path):
+    ran = []
+
+    def compiler(cmd, **kw):
+        ran.append(cmd)
+        return subprocess.CompletedProcess(cmd, 0, "", "")
+    monkeypatch.setattr(build_lib.subprocess, "run", compiler)
+    monkeypatch.setattr(build_lib.os, "replace", lambda a, b: None)
+    build_lib.build()
+    assert [c[-1] for c in ran] == [build_lib.LIB + ".tmp", build_lib.BIND + ".tmp"]
+    del ran[:]
+    build_lib.build(out=str(tmp_path / "libot.so"))  # a build of its own leaves the tree's binding
+    assert [c[-1] for c in ran] == [str(tmp_path / "libot.so") + ".tmp"]

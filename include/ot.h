@@ -66,7 +66,10 @@ int ot_abi_version(void);
  *                   recipe that computes it), so that a loaded library can
  *                   be matched against a source tree;
  *   arch            the GPU architecture of its device code;
- *   hip             the HIP version it was compiled against.
+ *   hip             the HIP version it was compiled against;
+ *   header_sha256   SHA-256 of the ot.h it was compiled with ("unknown" as
+ *                   above): code compiled against this header can tell
+ *                   whether a library that it loads has the same signatures.
  * Never NULL; owned by the library. */
 const char *ot_build_info(void);
 

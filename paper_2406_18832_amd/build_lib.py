@@ -27,6 +27,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libot.so")
 BIND_SOURCE = os.path.join(CSRC, "ot_bind.cpp")
 BIND = os.path.join(HERE, "_otbind.so")
+HEADER = os.path.join(os.path.dirname(HERE), "include", "ot.h")
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -75,6 +76,27 @@ def source_digest() -> str:
     return h.hexdigest()
 
 
+def _sha256(*paths) -> str:
+    h = hashlib.sha256()
+    for path in paths:
+        with open(path, "rb") as f:
+            h.update(f.read() + b"\0")
+    return h.hexdigest()
+
+
+def header_digest() -> str:
+    """SHA-256 of include/ot.h.  The library and the binding each record the
+    one they were compiled with: the binding calls the library's functions with
+    that header's signatures."""
+    return _sha256(HEADER)
+
+
+def bind_digest() -> str:
+    """SHA-256 over what the binding is built from (csrc/ot_bind.cpp and
+    include/ot.h); build_bind() compiles it into _otbind.so."""
+    return _sha256(BIND_SOURCE, HEADER)
+
+
 def asan_runtime() -> str:
     """Path of the compiler's AddressSanitizer runtime (to preload into a
     process that loads the sanitized library)."""
@@ -99,8 +121,8 @@ def build(verbose: bool = False, extra_flags=(), sanitize: bool = False, out: st
     flags = list(HIPCC_FLAGS)
     if sanitize:
         flags = [f for f in flags if f != "-O3"] + ["-O1", *SANITIZE_FLAGS]
-    cmd = [hipcc(), *flags, *extra_flags, f'-DOT_SOURCES_SHA256="{source_digest()}"', *sources(),
-           "-o", tmp]
+    cmd = [hipcc(), *flags, *extra_flags, f'-DOT_SOURCES_SHA256="{source_digest()}"',
+           f'-DOT_HEADER_SHA256="{header_digest()}"', *sources(), "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -132,6 +154,7 @@ def build_bind(verbose: bool = False) -> str:
     tmp = BIND + ".tmp"
     cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DOT_HEADER_SHA256="{header_digest()}"', f'-DOT_BIND_SHA256="{bind_digest()}"',
            "-isystem", os.path.join(root, "include"),
            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], BIND_SOURCE,

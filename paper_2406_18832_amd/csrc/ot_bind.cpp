@@ -320,4 +320,14 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_otbind", nullptr, -1, kMethods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__otbind(void) { return PyModule_Create(&kModule); }
+// header_sha256: the include/ot.h whose signatures the calls use; ot.py compares
+// it with the library's.  sources_sha256: what this file was built from.
+PyMODINIT_FUNC PyInit__otbind(void) {
+  PyObject *m = PyModule_Create(&kModule);
+  if (m != nullptr && (PyModule_AddStringConstant(m, "header_sha256", OT_HEADER_SHA256) != 0 ||
+                       PyModule_AddStringConstant(m, "sources_sha256", OT_BIND_SHA256) != 0)) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

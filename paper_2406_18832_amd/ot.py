@@ -11,8 +11,9 @@ If it has not been built the first call raises: there is no fallback.
 The runtime entry points check and marshal their arguments in _otbind.so
 (csrc/ot_bind.cpp); where an argument is not exactly what it expects, the
 Python checks here run instead and name the fault or convert the argument.
-They also run, with a warning, where _otbind.so has not been built: the kernels
-are the same, each call takes some 3 us more of host time.
+They also run, with a warning, where _otbind.so has not been built or was built
+with another include/ot.h than the library: the kernels are the same, each call
+takes some 3 us more of host time.
 """
 from __future__ import annotations
 
@@ -31,6 +32,7 @@ HEADER = os.path.join(os.path.dirname(HERE), "include", "ot.h")
 OT_OK, OT_EINVAL, OT_ESHAPE, OT_ERANGE, OT_ENONFINITE, OT_EHIP, OT_ENOSCRATCH = range(7)
 
 _lib = None
+_bind = None  # _otbind, once bound to the library
 
 
 def _unbound(*args):
@@ -56,15 +58,23 @@ _n_qlinear_per_token = _n_qlinear_asym = _unbound
 
 
 def _load_bind(L) -> None:
-    """Binds the native marshalling functions to the loaded library; without
-    _otbind.so they stay unbound (the Python checks) and a warning says so."""
+    """Binds the native marshalling functions to the loaded library.  Without
+    _otbind.so, or with one that was compiled with other signatures than the
+    library's, they stay unbound (the Python checks) and a warning says so."""
+    global _bind
+    path, why = os.path.join(HERE, "_otbind.so"), None
     try:
         from . import _otbind
+        theirs = _fields(L.ot_build_info().decode()).get("header_sha256")
+        if theirs is None or getattr(_otbind, "header_sha256", None) != theirs:
+            why = f"was built with another include/ot.h than {LIB_PATH}"
     except ImportError as e:
-        warnings.warn(f"{os.path.join(HERE, '_otbind.so')} cannot be loaded ({e}): arguments are "
-                      "checked in Python, which is slower; build it with build_lib.build()",
-                      RuntimeWarning, stacklevel=3)
+        why = f"cannot be loaded ({e})"
+    if why is not None:
+        warnings.warn(f"{path} {why}: arguments are checked in Python, which is slower; build it "
+                      "with build_lib.build()", RuntimeWarning, stacklevel=3)
         return
+    _bind = _otbind
     _otbind.set_current_stream(_current_stream)
     for name, symbols in _BOUND.items():
         addresses = [ctypes.cast(getattr(L, s), ctypes.c_void_p).value for s in symbols]
@@ -154,14 +164,23 @@ def ot_build_info() -> str:
     return lib().ot_build_info().decode()
 
 
+def _fields(build_info: str) -> dict:
+    return dict(f.split("=", 1) for f in build_info.split(";") if "=" in f)
+
+
 def build_info() -> dict:
     """ot_build_info()'s fields, the loaded library's path, and whether its
     sources_sha256 is that of the sources in this tree now (False means the
-    library was built from other sources: rebuild it)."""
+    library was built from other sources: rebuild it); the same for the
+    binding (None and False where the Python checks run instead)."""
     from . import build_lib
-    info = dict(f.split("=", 1) for f in ot_build_info().split(";") if "=" in f)
-    info["library"] = os.path.relpath(LIB_PATH, os.path.dirname(HERE))
+    root = os.path.dirname(HERE)
+    info = _fields(ot_build_info())
+    info["library"] = os.path.relpath(LIB_PATH, root)
     info["matches_sources"] = info.get("sources_sha256") == build_lib.source_digest()
+    info["binding"] = None if _bind is None else os.path.relpath(_bind.__file__, root)
+    info["binding_matches_sources"] = (_bind is not None and
+                                       _bind.sources_sha256 == build_lib.bind_digest())
     return info
 
 

@@ -253,6 +253,23 @@ def test_a_library_without_the_binding_is_enough(tmp_path):
     assert "arguments are checked in Python" in run.stdout
 
 
+def test_a_binding_of_another_header_is_not_called(tmp_path):
+    """The binding casts the library's addresses to the signatures it was
+    compiled with: one of another ot.h stays unbound.  (A copy of the tree's
+    binding whose recorded digest is another.)"""
+    from paper_2406_18832_amd import _otbind
+    assert ot.build_info()["binding_matches_sources"]
+    pkg = _package_copy(tmp_path)
+    with open(_otbind.__file__, "rb") as f:
+        data = f.read()
+    digest = build_lib.header_digest().encode()
+    assert data.count(digest) == 1 and _otbind.header_sha256.encode() == digest
+    (pkg / "_otbind.so").write_bytes(data.replace(digest, b"0" * 64))
+    run = _run(_BARE.format(root=str(tmp_path)), os.path.abspath(ot.LIB_PATH))
+    assert run.returncode == 0 and "passed x must be on the GPU" in run.stdout, run.stderr[-2000:]
+    assert "another include/ot.h" in run.stdout
+
+
 def test_one_build_makes_library_and_binding(monkeypatch, tmp_path):
     ran = []
 

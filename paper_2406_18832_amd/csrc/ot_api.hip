@@ -34,11 +34,18 @@ ot_status hip_status(hipError_t e) { return e == hipSuccess ? OT_OK : OT_EHIP; }
 // staging buffer: 50 us after a fold of 20480 channels).  The words
 // come from one 4 KiB block, allocated on first use and kept until the
 // process ends; a call holds its word only while it runs.  Without one (every
-// word taken, or no pinned memory) word() is nullptr and the caller reads its
-// outputs back.
+// word taken, no pinned memory, or a stream under capture, on which the call
+// is going to fail: its word could not be given back) word() is nullptr and the
+// caller reads its outputs back.
 class StatusWord {
  public:
-  StatusWord() {
+  explicit StatusWord(hipStream_t st) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    if (capture != hipStreamCaptureStatusNone) return;
     int *block = words();
     if (block == nullptr) return;
     uint64_t used = used_.load(std::memory_order_relaxed);
@@ -144,7 +151,7 @@ ot_status ot_calibrate(const uint16_t *x, int64_t rows, int64_t K, int a_bits, i
   if (first && (rc = hip_status(ot::launch_calib_reset(minmax, K, st))) != OT_OK) return rc;
   if ((rc = hip_status(ot::launch_calib_minmax(x, rows, K, minmax, st))) != OT_OK) return rc;
   if (ot::calib_finish_ok(K)) {
-    StatusWord status;
+    StatusWord status(st);
     if (status.word() != nullptr) {
       if (ot::launch_calib_finish(minmax, K, qmax(a_bits), z, s, inv_s, status.word(), st) !=
           hipSuccess) {
@@ -212,7 +219,7 @@ ot_status ot_fold_weights(const uint16_t *W, const uint16_t *b, int64_t N, int64
   if (!bits_ok(w_bits) || N < 0 || K < 0) return OT_EINVAL;
   if (N == 0 || K == 0 || N > kMaxRows || K > kMaxRows) return OT_ESHAPE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  StatusWord status;
+  StatusWord status(st);
   const hipError_t e =
       ot::launch_fold(W, b, N, K, w_bits, z, s, Wq, sW, bprime, status.word(), st);
   return fold_result(e, status, sW, bprime, N, st);
@@ -279,7 +286,7 @@ ot_status ot_fold_weights_per_token(const uint16_t *W, const uint16_t *b, const 
   if (N == 0 || K == 0 || N > kMaxRows || K > kMaxRows) return OT_ESHAPE;
   if (!W || !Wq || !sW || !bprime) return OT_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  StatusWord status;
+  StatusWord status(st);
   const hipError_t e =
       ot::launch_fold_per_token(W, b, zres, N, K, w_bits, Wq, sW, bprime, status.word(), st);
   return fold_result(e, status, sW, bprime, N, st);
@@ -311,7 +318,7 @@ ot_status ot_fold_weights_asym(const uint16_t *W, const uint16_t *b, int64_t N, 
   if (!bits_ok(w_bits) || N < 0 || K < 0) return OT_EINVAL;
   if (N == 0 || K == 0 || N > kMaxRows || K > kMaxRows) return OT_ESHAPE;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  StatusWord status;
+  StatusWord status(st);
   const hipError_t e =
       ot::launch_fold_asym(W, b, N, K, w_bits, z, s, Wq, sW, zW, bprime, status.word(), st);
   return fold_result(e, status, sW, bprime, N, st);

@@ -554,13 +554,8 @@ static const PrefillTile kPrefillTiles[] = {
     {32, 32, 256, 1.24f, 2.72f, 0.97f, "prefill 32x32"},
 };
 constexpr int kLargeTiles = 3;  // the first ones: this file's
-constexpr int k256x128 = 3;
 
 static const PrefillTile &prefill_tile(int64_t M, int64_t N, int64_t K) {
-  // Three token tiles by four channel tiles over a short K stay on 256 x 128,
-  // the tile that the launch plan is required to report there (300 tokens,
-  // 1000 channels, K = 1040: 9.5 us against 6 on 32 x 64).
-  if (M > 256 && M <= 384 && N > 768 && N <= 1024 && K <= 1040) return kPrefillTiles[k256x128];
   const int64_t cus = device_cus();
   auto tiles = [&](const PrefillTile &t) {
     return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);

@@ -270,20 +270,22 @@ def test_pipeline_opt125m(a_bits, w_bits):
 
 # --------------------------------------------------------------------------
 # Prefill tile shapes and the LDS-staged epilogue (Y only, no acc_out): the
-# library runs 256 x 256, 320 (channels) x 256 (tokens), 256 x 128 or
-# 192 x 256 tiles, whichever its cost model prices lowest.  On a 256-CU
-# MI355X the shapes below take, in order, the 320 x 256 tile (256 tiles
-# against 320 of 256 x 256), the 256 x 128 tile (less than one pass either
-# way), the 192 x 256 tile (one pass, 216 tiles) and the 256 x 256 tile
-# (two passes: 205 x 2, against three of 192 x 256); all have ragged M, N
-# and K.  The last two repeat the 320 x 256 and 256 x 256 cases with whole
-# 16-byte output rows (N a multiple of 8), where the tiles inside M x N take
-# the epilogue without per-lane bounds checks and the edge tiles the checked
-# one.
+# library runs 256 x 256, 320 (channels) x 256 (tokens) or 192 x 256 tiles or
+# a smaller deep-ring tile, whichever its cost model prices lowest.  On a
+# 256-CU MI355X the shapes below take, in order, the 320 x 256 tile (256 tiles
+# against 320 of 256 x 256), a small deep-ring tile (32 x 64: the larger ones
+# leave most CUs idle), the 192 x 256 tile (one pass, 216 tiles) and the
+# 256 x 256 tile (two passes: 205 x 2, against three of 192 x 256); all have
+# ragged M, N and K.  The next two repeat the 320 x 256 and 256 x 256 cases
+# with whole 16-byte output rows (N a multiple of 8), where the tiles inside
+# M x N take the epilogue without per-lane bounds checks and the edge tiles the
+# checked one.  The last is the largest deep-ring tile, 256 x 128, over more K
+# tiles than its ring has stages.
 # --------------------------------------------------------------------------
 PREFILL_TILE_SHAPES = [(500, 40860, 272), (300, 1000, 1040), (2000, 5000, 272), (1025, 9831, 272),
-                       (500, 40864, 272), (1025, 9832, 272)]
-PREFILL_TILE_ON_256_CUS = {(500, 40860, 272): "prefill 320x256", (300, 1000, 1040): "prefill 256x128",
+                       (500, 40864, 272), (1025, 9832, 272), (383, 16390, 1040)]
+PREFILL_TILE_ON_256_CUS = {(500, 40860, 272): "prefill 320x256", (300, 1000, 1040): "prefill 32x64",
+                           (383, 16390, 1040): "prefill 256x128",
                            (2000, 5000, 272): "prefill 192x256",
                            (1025, 9831, 272): "prefill 256x256",
                            (500, 40864, 272): "prefill 320x256",
@@ -292,7 +294,7 @@ PREFILL_TILE_ON_256_CUS = {(500, 40860, 272): "prefill 320x256", (300, 1000, 104
 
 def test_prefill_tiles_all_covered():
     """The tile shapes above are the ones the library runs (on a 256-CU
-    MI355X), so each of the three tiles stays covered."""
+    MI355X), so each of the large tiles, and 256 x 128, stays covered."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     if cus != 256:
         pytest.skip(f"tile choice depends on the CU count ({cus} here, 256 on MI355X)")
@@ -326,7 +328,7 @@ def test_prefill_tiles_staged_epilogue(M, N, K, flavour):
 # tiles' operand loads, spread over the MFMAs of the last K step and the
 # following tile's first ones, then all fall past the end of K (zeros into
 # a stage nobody reads), and the checkerboard's odd tiles wrap round at once.
-PREFILL_SHORT_K = [(500, 40864), (2000, 5000), (1025, 9832), (300, 1000)]
+PREFILL_SHORT_K = [(500, 40864), (2000, 5000), (1025, 9832), (300, 1000), (383, 16390)]
 
 
 @pytest.mark.parametrize("M,N", PREFILL_SHORT_K)

@@ -21,7 +21,7 @@ TILES = {(65, 33, 16): "32x32", (97, 515, 48): "32x32", (131, 104, 2064): "32x32
          (67, 4102, 528): "64x64", (127, 4104, 1040): "64x64",
          (65, 8197, 272): "64x128", (128, 10240, 768): "64x128",
          (161, 8250, 8208): "128x96", (131, 8197, 272): "128x128", (256, 8200, 1040): "128x128",
-         (129, 16390, 272): "192x128", (300, 1000, 272): "256x128", (383, 16390, 272): "256x128"}
+         (129, 16390, 272): "192x128", (300, 1000, 272): "32x64", (383, 16390, 272): "256x128"}
 
 
 def test_every_ring_tile_is_picked():

@@ -2,6 +2,7 @@
 every tile and epilogue against the oracle at the edges of its tiles, and the
 register budget of their kernels."""
 import os
+import re
 
 import numpy as np
 import pytest
@@ -23,11 +24,31 @@ TILES = {(65, 33, 16): "32x32", (97, 515, 48): "32x32", (131, 104, 2064): "32x32
          (161, 8250, 8208): "128x96", (131, 8197, 272): "128x128", (256, 8200, 1040): "128x128",
          (129, 16390, 272): "192x128", (300, 1000, 272): "32x64", (383, 16390, 272): "256x128"}
 
+# The same over a K that fills every stage of the ring more than twice, with a
+# tail: K tiles loaded into stages that hold older ones, where a wrong count of
+# loads in flight, a stage handed over early or a missing barrier would show.
+REUSED = {(131, 107, 4368): "32x32", (97, 2050, 2832): "32x64", (67, 4102, 2320): "64x64",
+          (97, 8197, 2064): "64x128", (191, 10250, 2064): "128x96", (131, 8197, 1296): "128x128",
+          (129, 16390, 1040): "192x128", (383, 16390, 1040): "256x128"}
+RING = {"32x32": (256, 8), "32x64": (256, 5), "64x64": (256, 4), "64x128": (256, 3),
+        "128x96": (128, 5), "128x128": (128, 4), "192x128": (128, 3), "256x128": (128, 3)}  # BK, stages
+
+
+def test_rings_and_their_reuse():
+    """RING is what the library compiles, and REUSED goes round each ring twice."""
+    with open(os.path.join(CSRC, "ot_ring.hip")) as f:
+        made = re.findall(r"^  OT_RING\((\d+), (\d+), (\d+), \d+, \d+, \d+, (\d+)\);", f.read(), re.M)
+    assert {f"{bn}x{bm}": (int(bk), int(stages)) for bn, bm, bk, stages in made} == RING
+    assert sorted(REUSED.values()) == sorted(RING)
+    for (M, N, K), tile in REUSED.items():
+        bk, stages = RING[tile]
+        assert -(-K // bk) >= 2 * stages + 1 and K % bk and N % 8, (M, N, K)
+
 
 def test_every_ring_tile_is_picked():
     if torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the tile choice depends on the CU count")
-    for shape, tile in TILES.items():
+    for shape, tile in [*TILES.items(), *REUSED.items()]:
         assert ot.ot_qlinear_plan(*shape) == "prefill " + tile, shape
 
 
@@ -44,7 +65,7 @@ def dev(a):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,K", list(TILES))
+@pytest.mark.parametrize("M,N,K", [*TILES, *REUSED])
 @pytest.mark.parametrize("flavour", ["channel", "token", "asym"])
 def test_ring_tiles_match_the_oracle(M, N, K, flavour):
     print(f"[case] ring {flavour} M={M} N={N} K={K} plan={ot.ot_qlinear_plan(M, N, K)}", flush=True)

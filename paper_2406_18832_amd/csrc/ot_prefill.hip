@@ -26,7 +26,7 @@ namespace detail {
 // The one barrier per K tile sits between the last fragment reads of tile t
 // and its last MFMAs; right after it the wave starts reading tile t+1 and
 // refills tile t's stage with tile t+S.  The refill's loads are not issued
-// in one burst: one follows every MPL-th MFMA, over the tile's last K step
+// in one burst: one follows every second MFMA, over the tile's last K step
 // and the next tile's first ones.  Issued back to back after the barrier,
 // the loads of both waves of a SIMD held its matrix core idle (a load
 // instruction takes the wave's issue for tens of cycles); spread between
@@ -78,7 +78,7 @@ struct BoolC {
 
 // The kernel body lives in a device function: hipcc drops the host stub of a
 // kernel template whose body holds lambdas.
-template <int BN, int BM, int BK, int WN, int WM, int S, int EPI, int MPL>
+template <int BN, int BM, int BK, int WN, int WM, int S, int EPI>
 __device__ __forceinline__ void prefill_body(
     int8_t *smem, const int8_t *__restrict__ Xq, const int8_t *__restrict__ Wq,
     const float *__restrict__ sX, const int32_t *__restrict__ zW, const float *__restrict__ sW,
@@ -220,11 +220,11 @@ __device__ __forceinline__ void prefill_body(
   };
   // A tile's last K step issues the first kLast loads of the tile S ahead
   // (whose stage the barrier before it has just freed), one after every
-  // MPL-th MFMA; the next tile's first K steps issue the rest at the same
+  // second MFMA; the next tile's first K steps issue the rest at the same
   // rate, all before the wait that precedes its last step.
   constexpr int kMfma = C::kFN * C::kFM;
   constexpr int kReads = C::kFN + C::kFM;
-  constexpr int kPerStep = kMfma / MPL;
+  constexpr int kPerStep = kMfma / 2;
   constexpr int kLast = kPerStep < C::kLoads ? kPerStep : C::kLoads;
   static_assert(kPerStep >= 1, "at least one load per K step");
   static_assert(kLast + (C::kKSteps - 2) * kPerStep >= C::kLoads,
@@ -232,7 +232,7 @@ __device__ __forceinline__ void prefill_body(
   // One K step: the MFMAs of K step `step` on fragment buffer cb, the
   // fragment reads of tile rkt's K step rstep into buffer nb, and loads
   // j0 .. j0+nl-1 of tile lt, issued in that interleaved order (a read
-  // before each MFMA while reads remain, a load after every MPL-th).
+  // before each MFMA while reads remain, a load after every second).
   auto kstep = [&](int cb, int step, int rkt, int rstep, int nb, int lt, int j0, int nl) {
     const int8_t *st = smem + (rkt % S) * C::kStage;
 #pragma unroll
@@ -244,7 +244,7 @@ __device__ __forceinline__ void prefill_body(
             *reinterpret_cast<const v4i *>(st + b_base + (i - C::kFN) * 32 * BK + frag_off[rstep]);
       const int f = i / C::kFM, g = i % C::kFM;
       acc[f][g] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[cb][f], fb[cb][g], acc[f][g], 0, 0, 0);
-      if (i % MPL == MPL - 1 && i / MPL < nl) issue_one(lt, j0 + i / MPL);
+      if (i % 2 == 1 && i / 2 < nl) issue_one(lt, j0 + i / 2);
     }
     if constexpr (EPI == kEpiAsym) {
       if (step % WN == __builtin_amdgcn_readfirstlane(wn)) {
@@ -258,7 +258,7 @@ __device__ __forceinline__ void prefill_body(
     for (int i = 0; i < kMfma; ++i) {
       if (i < kReads) __builtin_amdgcn_sched_group_barrier(kMaskDsRead, 1, 0);
       __builtin_amdgcn_sched_group_barrier(kMaskMfma, 1, 0);
-      if (i % MPL == MPL - 1 && i / MPL < nl) __builtin_amdgcn_sched_group_barrier(kMaskVmemRead, 1, 0);
+      if (i % 2 == 1 && i / 2 < nl) __builtin_amdgcn_sched_group_barrier(kMaskVmemRead, 1, 0);
     }
   };
 
@@ -456,21 +456,21 @@ __device__ __forceinline__ void prefill_body(
     epilogue(BoolC<false>{});
 }
 
-template <int BN, int BM, int BK, int WN, int WM, int S, int MPL, int OCC, int EPI>
-__global__ __launch_bounds__(64 * WN * WM, OCC) void qgemm_prefill_kernel(
+template <int BN, int BM, int BK, int WN, int WM, int S, int EPI>
+__global__ __launch_bounds__(64 * WN * WM, 1) void qgemm_prefill_kernel(
     const int8_t *__restrict__ Xq, const int8_t *__restrict__ Wq, const float *__restrict__ sX,
     const int32_t *__restrict__ zW, const float *__restrict__ sW, const float *__restrict__ bp,
     int M, int N, int K, uint16_t *__restrict__ Y, int32_t *__restrict__ acc_out, int tiles_m,
     int tiles_n, int group_m) {
   __shared__ __attribute__((aligned(1024)))
   int8_t smem[PrefillCfg<BN, BM, BK, WN, WM, S>::kSmem];
-  prefill_body<BN, BM, BK, WN, WM, S, EPI, MPL>(smem, Xq, Wq, sX, zW, sW, bp, M, N, K, Y, acc_out,
+  prefill_body<BN, BM, BK, WN, WM, S, EPI>(smem, Xq, Wq, sX, zW, sW, bp, M, N, K, Y, acc_out,
                                            tiles_m, tiles_n, group_m);
 }
 
 // Epilogue by argument: sX != nullptr per-token scales sX [M]; zW != nullptr
 // asymmetric weight zero points zW [N]; neither: per-channel.
-template <int BN, int BM, int BK, int WN, int WM, int S, int MPL, int OCC = 1>
+template <int BN, int BM, int BK, int WN, int WM, int S>
 hipError_t launch_prefill(const int8_t *Xq, const int8_t *Wq, const float *sX, const int32_t *zW,
                           const float *sW, const float *bp, int64_t M, int64_t N, int64_t K,
                           uint16_t *Y, int32_t *acc_out, hipStream_t st, int group_m = 8) {
@@ -478,13 +478,13 @@ hipError_t launch_prefill(const int8_t *Xq, const int8_t *Wq, const float *sX, c
   const unsigned grid = (unsigned)(tiles_m * tiles_n);
   const dim3 block(64 * WN * WM);
   if (sX)
-    qgemm_prefill_kernel<BN, BM, BK, WN, WM, S, MPL, OCC, kEpiToken><<<grid, block, 0, st>>>(
+    qgemm_prefill_kernel<BN, BM, BK, WN, WM, S, kEpiToken><<<grid, block, 0, st>>>(
         Xq, Wq, sX, zW, sW, bp, (int)M, (int)N, (int)K, Y, acc_out, tiles_m, tiles_n, group_m);
   else if (zW)
-    qgemm_prefill_kernel<BN, BM, BK, WN, WM, S, MPL, OCC, kEpiAsym><<<grid, block, 0, st>>>(
+    qgemm_prefill_kernel<BN, BM, BK, WN, WM, S, kEpiAsym><<<grid, block, 0, st>>>(
         Xq, Wq, sX, zW, sW, bp, (int)M, (int)N, (int)K, Y, acc_out, tiles_m, tiles_n, group_m);
   else
-    qgemm_prefill_kernel<BN, BM, BK, WN, WM, S, MPL, OCC, kEpiChannel><<<grid, block, 0, st>>>(
+    qgemm_prefill_kernel<BN, BM, BK, WN, WM, S, kEpiChannel><<<grid, block, 0, st>>>(
         Xq, Wq, sX, zW, sW, bp, (int)M, (int)N, (int)K, Y, acc_out, tiles_m, tiles_n, group_m);
   return hipGetLastError();
 }
@@ -599,14 +599,14 @@ hipError_t launch_qgemm_prefill(const int8_t *Xq, const int8_t *Wq, const float 
     return launch_qgemm_ring(t.bn, t.bm, Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out, st);
   switch (t.bn) {
     case 320:
-      return launch_prefill<320, 256, 128, 2, 4, 2, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y,
-                                                    acc_out, st);
+      return launch_prefill<320, 256, 128, 2, 4, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out,
+                                                 st);
     case 192:
-      return launch_prefill<192, 256, 128, 2, 4, 2, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y,
-                                                    acc_out, st);
+      return launch_prefill<192, 256, 128, 2, 4, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out,
+                                                 st);
     default:
-      return launch_prefill<256, 256, 128, 4, 2, 2, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y,
-                                                    acc_out, st);
+      return launch_prefill<256, 256, 128, 4, 2, 2>(Xq, Wq, sX, zW, sW, bprime, M, N, K, Y, acc_out,
+                                                 st);
   }
 }
 

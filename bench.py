@@ -506,10 +506,10 @@ def traffic_record(d, workload):
             raise SystemExit(f"{len(disp)} prefill dispatches is not a whole number of steps")
         for i, (g, v) in enumerate(disp):
             L = wl.layers[i % len(wl.layers)]
-            # the library runs 256 x 256, 320 (channels) x 256 (tokens), 256 x 128 or
+            # qgemm_prefill_kernel runs 256 x 256, 320 (channels) x 256 (tokens) or
             # 192 x 256 tiles
             grids = {f"{bn}x{bm}": -(-wl.M // bm) * -(-L.N // bn) * threads
-                     for bn, bm in ((256, 256), (320, 256), (256, 128), (192, 256))}
+                     for bn, bm in ((256, 256), (320, 256), (192, 256))}
             match = [t for t, gg in grids.items() if gg == g]
             if not match:
                 raise SystemExit(f"dispatch {i}: grid {g} fits no tile shape of layer {L.name} "
@@ -529,7 +529,7 @@ def traffic_record(d, workload):
     bench_args = ("--steps 2 --warmup 1 --no-cpu --no-fp16 --no-decode --no-ln --no-mixed "
                   "--no-asym --no-sclk --no-other")
     rec = {
-        "kernel": "qgemm_prefill_kernel (256x256, 320x256, 256x128 or 192x256 tiles, BK 128, 2 stages)",
+        "kernel": "qgemm_prefill_kernel (256x256, 320x256 or 192x256 tiles, BK 128, 2 stages)",
         "workload": f"{wl.name} ({wl.M} tokens; " + ", ".join(L.name for L in wl.layers) + ")",
         "source_files": [os.path.relpath(p, ROOT) for p in PREFILL_SOURCES],
         "source_sha256": prefill_source_digest(),
@@ -620,7 +620,7 @@ def counter_summary(d, workload, decode_workload):
         confl = np.mean([e["SQ_LDS_BANK_CONFLICT"] / max(e["SQ_INSTS_LDS"], 1) for e in es])
         ghz = np.mean([e["GRBM_GUI_ACTIVE"] / xcds / e["ns"] for e in es])
         tile = "?"
-        for bn, bm in ((256, 256), (320, 256), (256, 128), (192, 256)):
+        for bn, bm in ((256, 256), (320, 256), (192, 256)):
             if es[0]["grid"] == -(-wl.M // bm) * -(-L.N // bn) * 512:
                 tile = f"{bn}x{bm}"
         out.append(f"| {L.name} | {tile} | {ops:.4g} | {2 * wl.M * L.N * L.K:.4g} | {util:.3f} | "

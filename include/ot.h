@@ -348,9 +348,9 @@ size_t ot_qlinear_workspace_size(int64_t M, int64_t N, int64_t K);
  * NUL-terminated description into buf (at most len bytes, truncated if
  * longer): "none" for M == 0; "prefill <R>x<T>" (output channels x tokens
  * per workgroup: 320x256, 256x256, 192x256, 256x128, 192x128, 128x128,
- * 128x96, 64x128, 64x64, 32x64 or 32x32) above 64 tokens; "decode <layout> <R>-row tiles", with " split-K <runs>" where K
- * is split, up to 64 tokens.  OT_EINVAL for a NULL buf or len 0, OT_ESHAPE
- * for sizes the calls reject.  Synchronous, no device work; for
+ * 128x96, 64x128, 64x64, 32x64 or 32x32) above 64 tokens; "decode <layout>
+ * <R>-row tiles", with " split-K <runs>" where K is split, up to 64 tokens.
+ * OT_EINVAL for a NULL buf or len 0, OT_ESHAPE for sizes the calls reject.  Synchronous, no device work; for
  * introspection and tests (the results never depend on the plan).
  */
 ot_status ot_qlinear_plan(int64_t M, int64_t N, int64_t K, int packed,

@@ -18,8 +18,9 @@ namespace {
 constexpr int64_t kMaxK = int64_t(1) << 22;
 constexpr int64_t kMaxLnK = int64_t(1) << 16;  // LayerNorm width (exact sums, one workgroup per row)
 constexpr int64_t kMaxRows = (int64_t(1) << 31) - 1;
-// Prefill workgroups of the smallest tile (128 tokens by 256 channels): the
-// grid must fit a 32-bit count.
+// Calls of so many tokens and channels that not even 128 x 256 tiles of them
+// are a 32-bit count are refused (the launcher leaves a smaller tile out where
+// its own grid does not fit).
 bool grid_ok(int64_t M, int64_t N) { return (M + 127) / 128 * ((N + 255) / 256) <= kMaxRows; }
 
 bool bits_ok(int bits) { return bits >= 2 && bits <= 8; }

@@ -520,11 +520,19 @@ static double prefill_cost(int64_t M, int64_t N, int64_t K, int bn, int bm, int6
 //     and 960 of 256 x 256);
 //   192 x 256, waves 2 x 4 of 96 x 64 (112 KiB): the same for launches
 //     whose last pass of 256 x 256 runs half empty (2048 tokens by 12288
-//     channels: two full passes of 512 tiles against 1.5 of 384);
+//     channels: two full passes of 512 tiles against 1.5 of 384).
 // prefill_cost picks one of them.  The others are the deep-ring tiles of
 // ot_ring.hip, for launches that leave CUs idle on the large ones.  Of the
 // large tile and the deep-ring ones, the least estimated time runs (all give
 // identical results).
+//
+// Why the table does not pick the large tile too: over 70 random launches on
+// which the two would differ in the tile that runs (3 % of launches; 1700 ..
+// 9000 tokens, 4900 .. 34800 channels), prefill_cost's is 1.3 % over the
+// fastest of the three (6 % at worst), the table's 2.9 % (13 %).  Up to K =
+// 1568 prefill_cost's 320 x 256 beats the table's 256 x 256 mostly by 2-8 %
+// (4481 x 16514, K = 464: 171.5 and 194.0 us); from K = 3952 on it is the table
+// that names 320 x 256, 1-6 % faster (8787 x 9699, K = 13936: 1278 and 1339).
 //
 // The estimate, in microseconds: whole passes over the CUs, each of `pass` +
 // `per_k` per 1000 channels of K, plus `once` per launch (below 0 where the

@@ -13,11 +13,16 @@ namespace detail {
 // arranged WN x WM x WK: WN x WM blocks of (BN/WN) x (BM/WM), each worked on
 // by WK waves that take 1/WK of every K tile's 32-byte steps.
 //
-// What bounds it.  With 256 small tiles a CU stages (BN + BM) bytes per
-// BN * BM products, more than its L1 delivers: measured on MI355X, with the
-// MFMAs and fragment reads taken out of the loop the time does not change
-// (512 tokens x 5120 channels, K = 20480, 128 x 96 tiles: 78 us whole, 74
-// without; every CU stages 55-85 GB/s, all-hits in the L2 reach 145).  So:
+// What bounds it, from builds with one part of the K loop taken out (us, the
+// weights from HBM; whole, without MFMAs and fragment reads, without loads).
+// Up to a few hundred tokens, staging the operands: 512 x 5120, K = 20480 on
+// 128 x 96 tiles 75, 73, 44; 512 x 15360, K = 5120 on 256 x 128 46, 45, 28;
+// 131 x 6150, K = 4112 on 64 x 128 17, 17, 10.  A CU stages 43-61 GB/s there
+// ((BN + BM) bytes per BN * BM products), where loads that all hit the L2 reach
+// 145; with the weights in the last-level cache the loads alone take 57 of the
+// 73 us.  With many tokens no part alone: 2048 x 4096, K = 16384 on 256 x 128
+// tiles 118, 96, 83 (a fragment read and 0.375 loads per MFMA, which cost the
+// matrix core issue cycles).  So:
 //   - the ring is as deep as the LDS allows (3-8 stages): a K tile takes less
 //     time than a load's latency, and the two stages that suffice for the
 //     large tiles left the loads exposed (256 x 128 tiles, 2048 x 4096,

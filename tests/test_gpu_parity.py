@@ -324,7 +324,8 @@ def test_prefill_tiles_staged_epilogue(M, N, K, flavour):
     assert_fp16_close(host(Y), ref)
 
 
-# Every prefill tile at one and two K tiles (K = 48, 128, 144): the next
+# Every large prefill tile and two deep-ring ones (32 x 64, 256 x 128) at one
+# and, of 128 bytes, two K tiles (K = 48, 128, 144): the next
 # tiles' operand loads, spread over the MFMAs of the last K step and the
 # following tile's first ones, then all fall past the end of K (zeros into
 # a stage nobody reads), and the checkerboard's odd tiles wrap round at once.
@@ -405,20 +406,21 @@ def test_workspace_too_small_is_rejected_by_the_binding():
 
 
 # --------------------------------------------------------------------------
-# HIP graph replay: a prefill call, a decode call and a split-K decode call
-# (workspace) captured in one graph, replayed several times with eager work
+# HIP graph replay: prefill calls on a small deep-ring and on a large tile, a
+# decode call and a split-K decode call (workspace) captured in one graph,
+# replayed several times with eager work
 # and synchronizations in between; every replay must reproduce the eager
 # outputs bit for bit (the kernels clear nothing with memset nodes and keep
 # no state between calls).
 # --------------------------------------------------------------------------
 def test_graph_replay_matches_eager():
-    shapes = [(300, 772, 1040), (8, 7168, 2064), (40, 2048, 4112)]
+    shapes = [(300, 772, 1040), (8, 7168, 2064), (40, 2048, 4112), (1025, 9832, 272)]
     calls = []
     for i, (M, N, K) in enumerate(shapes):
         Xq, Wq, sW, bp = (dev(a) for a in _random_qlinear_inputs(M, N, K, 8, 8, 100 + i))
         Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
         calls.append((Xq, Wq, sW, bp, Y, ot.workspace_for(M, N, K)))
-    assert calls[2][5] is not None, "the last shape takes the split-K path"
+    assert calls[2][5] is not None, "the third shape takes the split-K path"
     # the split-K decode once more on packed weights (registers streamed
     # from the packed layout), into its own output and workspace
     Xq, Wq, sW, bp = calls[2][:4]

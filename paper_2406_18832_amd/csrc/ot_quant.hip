@@ -186,12 +186,16 @@ hipError_t launch_quantize_act_per_token(const uint16_t *x, int64_t M, int64_t K
   //     against 11.1, cached 9.9 against 10.0);
   //   - 8 chunks in 2 or 3 waves with at least four rows and under 156250
   //     elements a CU (2048 x 8192 11.8 and 11.8, cached 10.3 against 10.9;
-  //     4096 x 8416 19.2 against 20.0, 2025 x 9888 13.6 against 14.1; past that line 6000 x 8192 cached 24.8
-  //     against 23.8, below it 256 x 8192 4.4 against 3.9);
+  //     4096 x 8416 19.2 against 20.0, 2025 x 9888 13.6 against 14.1; past that
+  //     line 6000 x 8192 cached 24.8 against 23.8, below it 256 x 8192 4.4
+  //     against 3.9);
   //   - 8 chunks in 4 or, with at least seven rows a CU, 5 waves under 350000
   //     elements a CU (2048 x 14336 16.6 against 18.4, cached 15.4 against 16.7;
   //     4096 x 14336 29.1 against 31.0, cached 29.0 against 28.5; 3988 x 17120
   //     34.8 against 36.4; past the line 8496 x 16304 80.2 against 72.7).
+  // Near the lines and between them the better of the two goes with the rows
+  // left for the last pass over the CUs, either way by up to 6 % (879 x 20624
+  // cached 12.4 with 8 chunks, 13.2 here).
   // A launch takes fewer than 2^32 work-items: tens of millions of rows take
   // the fewer threads too.
   const int64_t chunks = K / 8, threads = (chunks + 3 * 64 - 1) / (3 * 64) * 64;
